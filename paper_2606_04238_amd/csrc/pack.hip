@@ -6,6 +6,8 @@
 // min-max with an integer zero point and a binary16 scale; the arithmetic is
 // IEEE fp64 with exactly one rounding of the scale to binary16, so every
 // code, scale and zero is reproducible bit for bit.
+#include <type_traits>
+
 #include "qmlp_device.h"
 #include "qmlp_internal.h"
 
@@ -57,79 +59,206 @@ __device__ uint32_t f64_to_f16_bits(double v) {
 
 __device__ double f16_bits_to_f64(uint32_t h) { return (double)h2f(h); }
 
-// One thread per (row, group).  W is [n][k] fp32; codes row-major words;
-// meta one uint32 per group: scale bits low, zero bits high.
-// 3 bits (Appendix B): a row is two planes, the low two bits of every code
-// in the 2-bit layout (k/16 words) followed by the high bit of every code
-// (k/32 words, code i at bit i mod 32 of word i/32 of the plane).
-template <int BITS>
-__global__ void __launch_bounds__(256)
-pack_kernel(const float* __restrict__ W, int n, int k, int g,
-            uint32_t* __restrict__ codes, uint32_t* __restrict__ meta, int32_t* status) {
-    constexpr int QMAX = (1 << BITS) - 1;
-    constexpr int PER = BITS == 3 ? 16 : 32 / BITS;       // codes per word (of the 2-bit plane)
-    const int ng = k / g;
-    const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (long)n * ng)
-        return;
-    const long row = gid / ng;
-    const long j = gid - row * ng;
-    const float* w = W + row * (long)k + j * (long)g;
-    const long row_words = BITS == 3 ? (long)k * 3 / 32 : (long)(k / PER);
-    uint32_t* out = codes + row * row_words + j * (long)(g / PER);
-    uint32_t* out_hi = codes + row * row_words + k / 16 + j * (long)(g / 32);   // 3 bits only
+// rint(w / sd) for a positive binary16 scale sd, exactly as IEEE fp64 division
+// followed by rint gives it, in fp32.  w has 24 significant bits and sd 11,
+// so w / sd is either a half integer exactly or at least 2^-23 of itself
+// away from one, and fp64 rounding never moves it onto one: the answer is the
+// integer nearest to the true quotient, ties to even.  c = rint(w * r) with
+// r = fl(1 / sd) is that integer or a neighbour (the quotient's magnitude is
+// at most 1.5 * 15 + 1, so the product is off by less than 1e-5), and the
+// remainder w - c sd is exact in fp32: it is a multiple of the smaller of the
+// two operands' last places and no larger than sd.
+__device__ __forceinline__ float div_rint(float w, float sd, float r) {
+    float c = __builtin_rintf(w * r);
+    const float rem = __builtin_fmaf(-c, sd, w);
+    const float twice = 2.0f * __builtin_fabsf(rem);
+    const float next = c + __builtin_copysignf(1.0f, rem);
+    const bool odd = ((int)c & 1) != 0;
+    return twice > sd || (twice == sd && odd) ? next : c;
+}
 
-    bool finite = true;
-    double lo = 0.0, hi = 0.0;
-    for (int i = 0; i < g; ++i) {
-        const double v = (double)w[i];
-        if (!__builtin_isfinite(v)) {
-            finite = false;
-        } else {
-            if (v < lo) lo = v;
-            if (v > hi) hi = v;
+// Min, max and OR of `bad` over the LPG consecutive lanes of a group (8, 16
+// or 32), in every lane.
+template <int LPG>
+__device__ __forceinline__ void group_range(float& lo, float& hi, uint32_t& bad) {
+    auto step = [&](float l2, float h2, uint32_t b2) {
+        lo = __builtin_fminf(lo, l2);
+        hi = __builtin_fmaxf(hi, h2);
+        bad |= b2;
+    };
+    auto d = [](uint32_t v, auto ctrl) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF, 0xF, false);
+    };
+    auto dstep = [&](auto ctrl) {
+        step(__uint_as_float(d(__float_as_uint(lo), ctrl)), __uint_as_float(d(__float_as_uint(hi), ctrl)),
+             d(bad, ctrl));
+    };
+    dstep(std::integral_constant<int, DPP_QUAD_XOR1>{});
+    dstep(std::integral_constant<int, DPP_QUAD_XOR2>{});
+    dstep(std::integral_constant<int, DPP_HALF_MIRROR>{});
+    if constexpr (LPG >= 16)
+        dstep(std::integral_constant<int, DPP_MIRROR>{});
+    if constexpr (LPG >= 32)
+        step(__shfl_xor(lo, 16, 64), __shfl_xor(hi, 16, 64), __shfl_xor(bad, 16, 64));
+}
+
+// Lane I of this lane's quad, to all four of them.
+template <int I>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, I * 0x55, 0xF, 0xF, false);
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t or_dpp(uint32_t v) {
+    return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+
+// W is [n][k] fp32; codes row-major words; meta one uint32 per group: scale
+// bits low, zero bits high.  At 2 and 4 bits codes, groups and weights are
+// flat arrays (rows are whole words and groups).  3 bits (Appendix B): a row
+// is two planes, the low two bits of every code in the 2-bit layout (k/16
+// words) followed by the high bit of every code (k/32 words, code i at bit
+// i mod 32 of word i/32 of the plane).
+//
+// What bounds it is reading W (4 bytes per weight against 0.3 to 0.7 written),
+// so a wave owns 1024 consecutive weights as four 16-byte loads per lane, each
+// load 1 KB contiguous, and a group is G / 4 consecutive lanes of one load.
+// The range is reduced between lanes; the fp64 arithmetic of scale and zero
+// (two divisions) is done once per lane for the load of its place in the
+// quad and handed to the other three by quad broadcasts, so it costs one
+// pass per 16 weights; the quotient of each weight is div_rint above.  Codes
+// of neighbouring lanes are OR-ed into words by quad moves.
+// One thread per group (a strided fp64 loop) took 3357 us for the three
+// matrices of a 4096 x 12288 block (196 GB/s); this takes
+// 163 us (4.0 TB/s, of 4.9 that a large copy reaches).
+template <int BITS, int G>
+__global__ void __launch_bounds__(256)
+pack_kernel(const float* __restrict__ W, long total, int k, uint32_t* __restrict__ codes,
+            uint32_t* __restrict__ meta, int32_t* status) {
+    constexpr int QMAX = (1 << BITS) - 1;
+    constexpr int LPG = G / 4;                            // lanes per group of one load
+    const int lane = threadIdx.x & 63;
+    const long base = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 1024;
+    if (base >= total)
+        return;
+    u32x4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const long e = base + 256 * i + 4 * lane;         // a group is inside total or past it as a whole
+        v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(W + (e < total ? e : 0)));
+    }
+    float lo = 0.0f, hi = 0.0f;                           // of the load of this lane's place in its quad
+    uint32_t bad = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float l = 0.0f, h = 0.0f;
+        uint32_t b = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t u = v[i][j];
+            const bool fin = (u & 0x7F800000u) != 0x7F800000u;
+            const float f = fin ? __uint_as_float(u) : 0.0f;
+            l = __builtin_fminf(l, f);
+            h = __builtin_fmaxf(h, f);
+            b |= fin ? 0u : 1u;
+        }
+        group_range<LPG>(l, h, b);
+        if ((lane & 3) == i) {
+            lo = l;
+            hi = h;
+            bad = b;
         }
     }
-    const double s = (hi - lo) / (double)QMAX;
+    const double s = ((double)hi - (double)lo) / (double)QMAX;
     uint32_t s16 = f64_to_f16_bits(s);
     if (s16 == 0)
-        s16 = 0x3C00u;                     // degenerate range: scale 1.0
-    if (!finite || s16 == 0x7C00u) {
-        for (int wd = 0; wd < g / PER; ++wd)
-            out[wd] = 0;
-        if (BITS == 3)
-            for (int wd = 0; wd < g / 32; ++wd)
-                out_hi[wd] = 0;
-        meta[gid] = 0x00007E00u;           // scale NaN, zero 0
-        if (status)
-            atomicOr(status, 1);
-        return;
-    }
-    const double sd = f16_bits_to_f64(s16);
-    double zf = __builtin_rint(-lo / sd);
+        s16 = 0x3C00u;                                    // degenerate range: scale 1.0
+    const bool invalid = bad != 0 || s16 == 0x7C00u;
+    const double sd64 = f16_bits_to_f64(s16);
+    double zf = __builtin_rint(-(double)lo / sd64);
     zf = zf < 0.0 ? 0.0 : (zf > (double)QMAX ? (double)QMAX : zf);
-    const int z = (int)zf;
-    uint32_t hbits = 0;                       // 3 bits: high bits of the current 32 codes
-    for (int wd = 0; wd < g / PER; ++wd) {
-        uint32_t word = 0;
-        for (int i = 0; i < PER; ++i) {
-            double t = __builtin_rint((double)w[wd * PER + i] / sd) + (double)z;
-            t = t < 0.0 ? 0.0 : (t > (double)QMAX ? (double)QMAX : t);
-            const uint32_t q = (uint32_t)t;
+    const float z1 = invalid ? 0.0f : (float)(int)zf;         // through int: never -0
+    const uint32_t m1 = invalid ? 0x00007E00u : s16 | (f2h(z1) << 16);   // invalid: scale NaN, zero 0
+    const float r1 = 1.0f / h2f(s16);
+
+    // codes of the four weights of each load
+    uint32_t q[4], qh[4];
+    auto load_codes = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t m = quad_bcast<i>(m1);
+        const float r = __uint_as_float(quad_bcast<i>(__float_as_uint(r1)));
+        const float sd = h2f(m & 0xFFFFu), z = h2f(m >> 16);
+        const bool ok = (m & 0xFFFFu) != 0x7E00u;
+        uint32_t word = 0, high = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float t = div_rint(__uint_as_float(v[i][j]), sd, r) + z;
+            const uint32_t c = ok ? (uint32_t)__builtin_fminf(__builtin_fmaxf(t, 0.0f), (float)QMAX) : 0u;
             if (BITS == 3) {
-                word |= (q & 3u) << (2 * i);
-                hbits |= (q >> 2) << ((wd * PER + i) & 31);
-                if (((wd * PER + i) & 31) == 31) {
-                    out_hi[(wd * PER + i) >> 5] = hbits;
-                    hbits = 0;
-                }
+                word |= (c & 3u) << (2 * j);
+                high |= (c >> 2) << j;
             } else {
-                word |= q << (BITS * i);
+                word |= c << (BITS * j);
             }
         }
-        out[wd] = word;
+        q[i] = word;
+        qh[i] = high;
+        const long e = base + 256 * i + 4 * lane;
+        if (lane % LPG == 0 && e < total) {
+            meta[e / G] = m;
+            if (!ok && status)
+                atomicOr(status, 1);
+        }
+    };
+    load_codes(std::integral_constant<int, 0>{});
+    load_codes(std::integral_constant<int, 1>{});
+    load_codes(std::integral_constant<int, 2>{});
+    load_codes(std::integral_constant<int, 3>{});
+
+    const int p = lane & 3, quad = lane >> 2;
+    if constexpr (BITS == 4) {
+        // a word is the halves of two lanes; lane p of a quad keeps load p's two words
+        uint32_t a = 0, b = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t w = or_dpp<DPP_QUAD_XOR1>(q[i] << (16 * (lane & 1)));
+            const uint32_t w0 = quad_bcast<0>(w), w1 = quad_bcast<2>(w);
+            if (p == i) {
+                a = w0;
+                b = w1;
+            }
+        }
+        const long e = base + 256 * p + 16 * quad;        // first code of the two words
+        if (e < total)
+            *reinterpret_cast<uint2*>(codes + e / 8) = make_uint2(a, b);
+    } else {
+        // a word is the bytes of a quad; lane p of a quad keeps load p's word
+        uint32_t a = 0, h = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t w = or_dpp<DPP_QUAD_XOR2>(or_dpp<DPP_QUAD_XOR1>(q[i] << (8 * p)));
+            if (p == i)
+                a = w;
+            if constexpr (BITS == 3) {
+                // the high plane's word is the nibbles of eight lanes
+                const uint32_t x = or_dpp<DPP_HALF_MIRROR>(
+                    or_dpp<DPP_QUAD_XOR2>(or_dpp<DPP_QUAD_XOR1>(qh[i] << (4 * (lane & 7)))));
+                if (p == i)
+                    h = x;
+            }
+        }
+        const long e = base + 256 * p + 16 * quad;        // first code of the word
+        if (e < total) {
+            if constexpr (BITS == 2) {
+                codes[e / 16] = a;
+            } else {
+                const long row = e / k, col = e - row * k;
+                uint32_t* out = codes + row * ((long)k * 3 / 32);
+                out[col / 16] = a;
+                if ((quad & 1) == 0)
+                    out[k / 16 + col / 32] = h;
+            }
+        }
     }
-    meta[gid] = s16 | (f2h((float)z) << 16);
 }
 
 // One thread per 32-bit code word: canonical codes uint8 [n][k]; the thread
@@ -210,15 +339,27 @@ dequant_kernel(const uint32_t* __restrict__ codes, const uint32_t* __restrict__ 
 
 static inline unsigned blocks_for(long threads) { return (unsigned)((threads + 255) / 256); }
 
+template <int BITS>
+static void pack_bits(const float* W, long total, int k, int g, uint32_t* codes, uint32_t* meta,
+                      int32_t* status, hipStream_t st) {
+    const unsigned grid = (unsigned)((total + 4095) / 4096);       // four waves of 1024 weights
+    if (g == 32)
+        pack_kernel<BITS, 32><<<grid, 256, 0, st>>>(W, total, k, codes, meta, status);
+    else if (g == 64)
+        pack_kernel<BITS, 64><<<grid, 256, 0, st>>>(W, total, k, codes, meta, status);
+    else
+        pack_kernel<BITS, 128><<<grid, 256, 0, st>>>(W, total, k, codes, meta, status);
+}
+
 hipError_t launch_pack(int bits, const float* W, int n, int k, int g, uint32_t* codes,
                        uint32_t* meta, int32_t* status, hipStream_t st) {
-    const long groups = (long)n * (k / g);
+    const long total = (long)n * k;
     if (bits == 2)
-        pack_kernel<2><<<blocks_for(groups), 256, 0, st>>>(W, n, k, g, codes, meta, status);
+        pack_bits<2>(W, total, k, g, codes, meta, status, st);
     else if (bits == 3)
-        pack_kernel<3><<<blocks_for(groups), 256, 0, st>>>(W, n, k, g, codes, meta, status);
+        pack_bits<3>(W, total, k, g, codes, meta, status, st);
     else
-        pack_kernel<4><<<blocks_for(groups), 256, 0, st>>>(W, n, k, g, codes, meta, status);
+        pack_bits<4>(W, total, k, g, codes, meta, status, st);
     return hipGetLastError();
 }
 
