@@ -91,10 +91,31 @@ qmlp_status check_mlp(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
     return QMLP_OK;
 }
 
+// Whether the one-kernel layer runs this block at M tokens (binary16).
+bool fused_mlp(const qmlp_mlp* mlp, int M) {
+    return standard_mlp(mlp) &&
+           fused_supported(M, mlp->gate.k_in, mlp->gate.n_out, mlp->gate.group, mlp->rank);
+}
+
+// Fewest tokens at which a half runs on the matrix-core tile kernels
+// (decode_tile.hip) instead of the stand-alone ones.
+constexpr int kTileMinTokens = 2;
+
+// Whether the gate/up half of a batch of nb such blocks takes the tile
+// kernels, and the slices of f its down half takes there (0: stand-alone).
+bool tile_gateup(const qmlp_mlp* mlp, int M, int nb) {
+    return M >= kTileMinTokens && tile_gateup_supported(M, mlp->gate.k_in, mlp->gate.n_out, mlp->gate.group,
+                                                        mlp->gate.bits, mlp->rank, nb);
+}
+int tile_slices(const qmlp_qweight* w, int M, int nb) {
+    return M >= kTileMinTokens ? tile_linear_slices(M, w->n_out, w->k_in, w->group, w->bits, nb) : 0;
+}
+
 // Workspace: [control words, 1 KB][t: fp32][h: M x f activation type]
 // [T: M x 2r bfloat16, prefill only][t64: one [4][64] copy of tagged words
 // per block of the one-kernel layer, h32: 4 x f tagged words -- decode only,
-// that kernel's hand-offs].  t is
+// that kernel's hand-offs; where the block runs on the tile kernels instead,
+// the same bytes hold the down slices' counters and partial sums, zero again after the call].  t is
 // M x 2r on the decode path and S x M x 2r split-K partials on the prefill
 // path.
 constexpr size_t kCtlBytes = 1024;
@@ -107,6 +128,8 @@ struct Workspace {
     unsigned long long* t64;
     uint32_t* h32;
     float* part;                // prefill down partial sums (bfloat16 chunks), else null
+    float* tile_t;              // decode without the one-kernel layer: the slices of LoRA-A
+    float* tile_scratch;        // and the down slices' counters and partial sums
 };
 
 size_t ws_t_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
@@ -130,6 +153,25 @@ size_t ws_total_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
            ws_tag_bytes(mlp, dtype) + ws_part_bytes(mlp, M, dtype);
 }
 
+size_t tile_t_bytes(const qmlp_mlp* mlp, int M) {
+    return round256((size_t)kLoraSlices * M * 2 * mlp->rank * 4);
+}
+// Slices of f of a batch's down half on the tile kernels (0: stand-alone).
+// More than one needs the gate/up half there as well, whose launch clears the
+// slices' counters.
+int down_slices(const qmlp_mlp* mlp, int M, int nb, bool gateup) {
+    const int sk = tile_slices(&mlp->down, M, nb);
+    return sk > 1 && !gateup ? 0 : sk;
+}
+bool block_tile_gateup(const qmlp_mlp* mlp, int M) {
+    return !fused_mlp(mlp, M) && tile_gateup(mlp, M, 1);
+}
+// ... of a single block: the scratch sits in the hand-off area.
+int block_slices(const qmlp_mlp* mlp, int M) {
+    const int sk = down_slices(mlp, M, 1, block_tile_gateup(mlp, M));
+    return tile_t_bytes(mlp, M) + tile_scratch_bytes(sk, 1, M, mlp->gate.k_in) <= ws_tag_bytes(mlp, QMLP_F16) ? sk : 0;
+}
+
 Workspace carve(const qmlp_mlp* mlp, int M, qmlp_dtype dtype, void* ws) {
     char* base = static_cast<char*>(ws);
     const size_t tb = ws_t_bytes(mlp, M, dtype), hb = ws_h_bytes(mlp, M);
@@ -140,7 +182,8 @@ Workspace carve(const qmlp_mlp* mlp, int M, qmlp_dtype dtype, void* ws) {
             reinterpret_cast<uint16_t*>(base + kCtlBytes + tb + hb),
             reinterpret_cast<unsigned long long*>(tag),
             reinterpret_cast<uint32_t*>(tag + (dtype == QMLP_F16 ? ws_t64_bytes() : 0)),
-            ws_part_bytes(mlp, M, dtype) ? reinterpret_cast<float*>(part) : nullptr};
+            ws_part_bytes(mlp, M, dtype) ? reinterpret_cast<float*>(part) : nullptr,
+            reinterpret_cast<float*>(tag), reinterpret_cast<float*>(tag + tile_t_bytes(mlp, M))};
 }
 
 // The prefill-chunk gate/up half: LoRA-A (split K + reduction), then the
@@ -210,18 +253,83 @@ DownArgs down_args(const qmlp_qweight* down, const void* h, int M, void* y) {
     return a;
 }
 
-// The gate/up half: LoRA-A projection then the fused kernel.
-qmlp_status run_gateup(const qmlp_mlp* mlp, const void* x, int M, uint16_t* h, float* t,
+StackLayerDesc stack_desc(const qmlp_mlp& m) {
+    StackLayerDesc s;
+    s.cg = static_cast<const uint32_t*>(m.gate.codes);
+    s.mg = static_cast<const uint32_t*>(m.gate.meta);
+    s.cu = static_cast<const uint32_t*>(m.up.codes);
+    s.mu = static_cast<const uint32_t*>(m.up.meta);
+    s.cd = static_cast<const uint32_t*>(m.down.codes);
+    s.md = static_cast<const uint32_t*>(m.down.meta);
+    s.Bg = static_cast<const uint16_t*>(m.B_gate);
+    s.Bu = static_cast<const uint16_t*>(m.B_up);
+    s.Ag = static_cast<const uint16_t*>(m.A_gate);
+    s.Au = static_cast<const uint16_t*>(m.A_up);
+    s.lora_scale = m.lora_scale;
+    return s;
+}
+
+// The shape and weights of one block as a batch of one.
+BatchArgs block_batch(const qmlp_mlp* mlp, int M) {
+    BatchArgs b{};
+    b.lay[0] = stack_desc(*mlp);
+    b.M = M;
+    b.d = mlp->gate.k_in;
+    b.f = mlp->gate.n_out;
+    b.r = mlp->rank;
+    b.gg = mlp->gate.group;
+    b.bg = mlp->gate.bits;
+    b.gd = mlp->down.group;
+    b.bd = mlp->down.bits;
+    return b;
+}
+
+// The gate/up half: LoRA-A projection then the fused kernel.  With `down` the
+// block's down half follows on the tile kernels, whose launch clears the
+// LoRA-A slices; alone, LoRA-A takes the one slice of t.
+qmlp_status run_gateup(const qmlp_mlp* mlp, const void* x, int M, uint16_t* h, const Workspace& w, bool down,
                        hipStream_t st) {
+    if (block_tile_gateup(mlp, M)) {
+        BatchArgs b = block_batch(mlp, M);
+        b.x = static_cast<const uint16_t*>(x);
+        b.h = h;
+        b.t = down ? w.tile_t : w.t;
+        const int ts = down ? kLoraSlices : 1;
+        hipError_t e = mlp->rank > 0 ? launch_lora_a_tile(b, 1, ts, st) : hipSuccess;
+        if (e == hipSuccess)
+            e = launch_gateup_tile(b, 1, ts, down && block_slices(mlp, M) > 1 ? w.tile_scratch : nullptr, st);
+        return from_hip(e);
+    }
     if (mlp->rank > 0) {
         hipError_t e = launch_lora_a(static_cast<const uint16_t*>(mlp->A_gate),
                                      static_cast<const uint16_t*>(mlp->A_up),
                                      static_cast<const uint16_t*>(x), M, mlp->gate.k_in,
-                                     mlp->rank, t, st);
+                                     mlp->rank, w.t, st);
         if (e != hipSuccess)
             return QMLP_ERR_HIP;
     }
-    return from_hip(launch_gateup(gateup_args(mlp, x, M, h, t), st));
+    return from_hip(launch_gateup(gateup_args(mlp, x, M, h, w.t), st));
+}
+
+// A linear [n][k] of up to 16 tokens: the tile kernels (sk slices of k, more
+// than one through `scratch`; clear_t floats of t go to zero), else the
+// stand-alone kernel.
+qmlp_status run_down(const qmlp_qweight* down, const void* h, int M, void* y, int sk, float* scratch,
+                     float* t, int clear_t, hipStream_t st) {
+    if (sk == 0 || (sk > 1 && !scratch))
+        return from_hip(launch_down(down_args(down, h, M, y), st));
+    BatchArgs b{};
+    b.lay[0].cd = static_cast<const uint32_t*>(down->codes);
+    b.lay[0].md = static_cast<const uint32_t*>(down->meta);
+    b.h = const_cast<uint16_t*>(static_cast<const uint16_t*>(h));
+    b.y = static_cast<uint16_t*>(y);
+    b.M = M;
+    b.d = down->n_out;
+    b.f = down->k_in;
+    b.gd = down->group;
+    b.bd = down->bits;
+    b.t = t;
+    return from_hip(launch_linear_tile(b, 1, clear_t, scratch, st));
 }
 
 qmlp_status pack_common(int bits, const float* W, int n_out, int k_in, int group,
@@ -294,22 +402,6 @@ size_t stack_layer_ws(const qmlp_mlp* layers, int M, qmlp_dtype dtype) {
     return round256(ws_total_bytes(layers, M, dtype));
 }
 
-StackLayerDesc stack_desc(const qmlp_mlp& m) {
-    StackLayerDesc s;
-    s.cg = static_cast<const uint32_t*>(m.gate.codes);
-    s.mg = static_cast<const uint32_t*>(m.gate.meta);
-    s.cu = static_cast<const uint32_t*>(m.up.codes);
-    s.mu = static_cast<const uint32_t*>(m.up.meta);
-    s.cd = static_cast<const uint32_t*>(m.down.codes);
-    s.md = static_cast<const uint32_t*>(m.down.meta);
-    s.Bg = static_cast<const uint16_t*>(m.B_gate);
-    s.Bu = static_cast<const uint16_t*>(m.B_up);
-    s.Ag = static_cast<const uint16_t*>(m.A_gate);
-    s.Au = static_cast<const uint16_t*>(m.A_up);
-    s.lora_scale = m.lora_scale;
-    return s;
-}
-
 // Independent blocks at one token in the W4/W2-GateUp form stream: every
 // batch of up to kBatchMax blocks is the LoRA-A launch, one persistent
 // gate/up launch and one persistent down launch (decode_stream.hip).
@@ -349,16 +441,31 @@ bool layers_batched(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
     return dtype == QMLP_F16 && !layers_streamed(layers, L, M, dtype) && !layers_mfma(layers, L, M, dtype);
 }
 
-enum class BatchPath { kBatched, kStreamed, kMfma };
+// kBatched: the stand-alone kernels alone; kTile: the tile kernels where
+// they take a half, the stand-alone ones otherwise.
+enum class BatchPath { kBatched, kStreamed, kMfma, kTile };
 
+// The tile kernels come before those of decode_mfma.hip where they take both
+// halves: 36 Qwen3-8B-shaped blocks at M = 4 and 16 measured 401 and 457
+// against 476 and 520 us, two Qwen3-4B-shaped ones at M = 4 41 against 63 us,
+// three 14B-class ones at M = 8 104 against 190 us (40 of them at M = 16: 1006
+// against 988).  Rows too long for them stay there.
 BatchPath batch_path(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
-    return layers_streamed(layers, L, M, dtype) ? BatchPath::kStreamed
-           : layers_mfma(layers, L, M, dtype)   ? BatchPath::kMfma
-                                                : BatchPath::kBatched;
+    const int n = L < kBatchMax ? L : kBatchMax;
+    if (layers_streamed(layers, L, M, dtype))
+        return BatchPath::kStreamed;
+    if (layers_mfma(layers, L, M, dtype) && !(tile_gateup(layers, M, n) && tile_slices(&layers[0].down, M, n) > 0))
+        return BatchPath::kMfma;
+    return BatchPath::kTile;
 }
 
-// t of a batch: [nb][M][2r] fp32, or kLoraSlices such arrays of partial
-// sums on the matrix-core path.
+// t of a batch: [nb][M][2r] fp32, kLoraSlices such arrays of partial sums on
+// the matrix cores, a tagged 64-bit word per value on the streamed path.
+int layers_t_slices(const qmlp_mlp* layers, int L, int M, BatchPath path) {
+    if (path == BatchPath::kTile)
+        return tile_gateup(layers, M, L < kBatchMax ? L : kBatchMax) ? kLoraSlices : 1;
+    return path == BatchPath::kStreamed ? 2 : path == BatchPath::kMfma ? kLoraSlices : 1;
+}
 size_t batch_t_bytes(const qmlp_mlp* a, int nb, int M, int slices = 1) {
     return round256((size_t)slices * nb * M * 2 * a->rank * 4);
 }
@@ -373,9 +480,14 @@ qmlp_status run_layers_batched(const qmlp_mlp* layers, int L, const char* xb, in
     const int d = a.gate.k_in;
     const size_t step = (size_t)M * d * 2;
     char* base = static_cast<char*>(ws);
-    // t: four fp32 partial sums per value on the matrix cores, one tagged
-    // 64-bit word on the streamed path, fp32 otherwise
-    const int ts = path == BatchPath::kMfma ? kLoraSlices : path == BatchPath::kStreamed ? 2 : 1;
+    // the tile kernels' down slices have their counters and fp32 partials after h
+    const int full = batch_size(L);
+    const bool tgu = path == BatchPath::kTile && tile_gateup(&a, M, full);
+    const int sk = path == BatchPath::kTile ? down_slices(&a, M, full, tgu) : 0;
+    const int ts = layers_t_slices(layers, L, M, path);
+    float* scratch = sk > 1 ? reinterpret_cast<float*>(base + kCtlBytes + batch_t_bytes(&a, full, M, ts) +
+                                                       batch_h_bytes(&a, full, M))
+                            : nullptr;
     BatchArgs b{};
     b.t = reinterpret_cast<float*>(base + kCtlBytes);
     b.h = reinterpret_cast<uint16_t*>(base + kCtlBytes + batch_t_bytes(&a, batch_size(L), M, ts));
@@ -396,14 +508,17 @@ qmlp_status run_layers_batched(const qmlp_mlp* layers, int L, const char* xb, in
         auto* t64 = reinterpret_cast<unsigned long long*>(b.t);
         hipError_t e = b.r == 0 || path == BatchPath::kStreamed ? hipSuccess   // streamed: in gate/up
                        : path == BatchPath::kMfma              ? launch_lora_a_mfma(b, n, st)
+                       : tgu                                   ? launch_lora_a_tile(b, n, kLoraSlices, st)
                                                                : launch_lora_a_batch(b, n, st);
         if (e == hipSuccess)
             e = path == BatchPath::kStreamed ? launch_gateup_stream(b, n, t64, ctl, st)
                 : path == BatchPath::kMfma   ? launch_gateup_mfma(b, n, st)
+                : tgu                        ? launch_gateup_tile(b, n, kLoraSlices, scratch, st)
                                              : launch_gateup_batch(b, n, st);
         if (e == hipSuccess)
             e = path == BatchPath::kStreamed ? launch_down_stream(b, n, ctl, st)
                 : path == BatchPath::kMfma   ? launch_down_mfma(b, n, st)
+                : sk > 0                     ? launch_linear_tile(b, n, 0, scratch, st)
                                              : launch_down_batch(b, n, st);
         if (e != hipSuccess)
             return QMLP_ERR_HIP;
@@ -492,7 +607,7 @@ qmlp_status qmlp_gateup_w2_lora(const qmlp_mlp* mlp, const void* x, int M, qmlp_
     if (dtype == QMLP_BF16)
         return run_prefill_gateup(mlp, x, M, static_cast<uint16_t*>(h), w,
                                   static_cast<hipStream_t>(stream));
-    return run_gateup(mlp, x, M, static_cast<uint16_t*>(h), w.t, static_cast<hipStream_t>(stream));
+    return run_gateup(mlp, x, M, static_cast<uint16_t*>(h), w, false, static_cast<hipStream_t>(stream));
 }
 
 qmlp_status qmlp_down_w4(const qmlp_qweight* down, const void* h, int M, qmlp_dtype dtype,
@@ -518,7 +633,8 @@ qmlp_status qmlp_down_w4(const qmlp_qweight* down, const void* h, int M, qmlp_dt
         return QMLP_ERR_ALIGN;
     if (dtype == QMLP_BF16)
         return run_prefill_down(down, h, M, y, nullptr, static_cast<hipStream_t>(stream));
-    return from_hip(launch_down(down_args(down, h, M, y), static_cast<hipStream_t>(stream)));
+    const int sk = tile_slices(down, M, 1);
+    return run_down(down, h, M, y, sk == 1 ? 1 : 0, nullptr, nullptr, 0, static_cast<hipStream_t>(stream));
 }
 
 qmlp_status qmlp_forward(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype dtype, void* y,
@@ -538,17 +654,18 @@ qmlp_status qmlp_forward(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype d
             return s;
         return run_prefill_down(&mlp->down, w.h, M, y, w.part, st);
     }
-    if (standard_mlp(mlp) &&
-        fused_supported(M, mlp->gate.k_in, mlp->gate.n_out, mlp->gate.group, mlp->rank))
+    if (fused_mlp(mlp, M))
         return from_hip(launch_fused(gateup_args(mlp, x, M, w.h, w.t),
                                      down_args(&mlp->down, w.h, M, y),
                                      static_cast<const uint16_t*>(mlp->A_gate),
                                      static_cast<const uint16_t*>(mlp->A_up), w.t64, w.h32, w.ctl,
                                      st));
-    s = run_gateup(mlp, x, M, w.h, w.t, st);
+    const int sk = block_slices(mlp, M);
+    s = run_gateup(mlp, x, M, w.h, w, sk > 0, st);
     if (s != QMLP_OK)
         return s;
-    return from_hip(launch_down(down_args(&mlp->down, w.h, M, y), st));
+    return run_down(&mlp->down, w.h, M, y, sk, w.tile_scratch, w.tile_t,
+                    block_tile_gateup(mlp, M) ? kLoraSlices * M * 2 * mlp->rank : 0, st);
 }
 
 qmlp_status qmlp_unpack(const qmlp_qweight* w, uint8_t* codes, uint16_t* scales, uint16_t* zeros,
@@ -584,8 +701,7 @@ int qmlp_forward_launches(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
     if (dtype == QMLP_BF16)
         return (mlp->rank > 0 ? 4 : 2) +
                (prefill_down_slices(M, mlp->gate.k_in, mlp->gate.n_out) > 1 ? 1 : 0);
-    if (standard_mlp(mlp) &&
-        fused_supported(M, mlp->gate.k_in, mlp->gate.n_out, mlp->gate.group, mlp->rank))
+    if (fused_mlp(mlp, M))
         return 1;
     return mlp->rank > 0 ? 3 : 2;
 }
@@ -680,11 +796,15 @@ qmlp_status qmlp_forward_stack(const qmlp_mlp* layers, int L, const void* x, int
 size_t qmlp_layers_workspace_bytes(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
     if (check_layers(layers, L, M, dtype) != QMLP_OK || M == 0)
         return 0;
-    if (dtype == QMLP_F16)              // streamed, matrix-core or batched
-        return kCtlBytes +
-               batch_t_bytes(layers, batch_size(L), M,
-                             layers_mfma(layers, L, M, dtype) ? kLoraSlices : layers_streamed(layers, L, M, dtype) ? 2 : 1) +
-               batch_h_bytes(layers, batch_size(L), M);
+    if (dtype == QMLP_F16) {            // streamed, matrix-core or batched
+        const int n = batch_size(L);
+        const BatchPath path = batch_path(layers, L, M, dtype);
+        const bool tile = path == BatchPath::kTile;
+        const bool tgu = tile && tile_gateup(layers, M, n);
+        const int ts = layers_t_slices(layers, L, M, path);
+        return kCtlBytes + batch_t_bytes(layers, n, M, ts) + batch_h_bytes(layers, n, M) +
+               (tile ? tile_scratch_bytes(down_slices(layers, M, n, tgu), n, M, layers[0].gate.k_in) : 0);
+    }
     return qmlp_workspace_bytes(&layers[0], M, dtype);
 }
 
@@ -703,9 +823,11 @@ int qmlp_layers_path(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
 int qmlp_layers_launches(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
     if (check_layers(layers, L, M, dtype) != QMLP_OK || M == 0)
         return 0;
-    if (dtype == QMLP_F16)              // three launches per batch (two streamed or without adapters)
+    if (dtype == QMLP_F16) {            // three launches per batch (two streamed or without adapters)
+        const BatchPath path = batch_path(layers, L, M, dtype);
         return (L + kBatchMax - 1) / kBatchMax *
-               (layers[0].rank > 0 && !layers_streamed(layers, L, M, dtype) ? 3 : 2);
+               (layers[0].rank > 0 && path != BatchPath::kStreamed ? 3 : 2);
+    }
     int n = 0;
     for (int i = 0; i < L; ++i) n += qmlp_forward_launches(&layers[i], M, dtype);
     return n;
@@ -806,7 +928,8 @@ qmlp_status qmlp_linear_batch(const qmlp_qweight* w, int L, const void* x, int M
     b.f = k;
     b.gd = w[0].group;
     b.bd = bits;
-    return from_hip(launch_down_batch(b, L, static_cast<hipStream_t>(stream)));
+    return from_hip(tile_slices(&w[0], M, L) == 1 ? launch_linear_tile(b, L, 0, nullptr, static_cast<hipStream_t>(stream))
+                                                  : launch_down_batch(b, L, static_cast<hipStream_t>(stream)));
 }
 
 size_t qmlp_moe_workspace_bytes(const qmlp_mlp* experts, int E, int M, int k, qmlp_dtype dtype) {

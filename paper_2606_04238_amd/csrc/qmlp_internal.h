@@ -172,6 +172,20 @@ constexpr int kLoraSlices = 4;
 hipError_t launch_lora_a_mfma(const BatchArgs& b, int nb, hipStream_t st);
 hipError_t launch_gateup_mfma(const BatchArgs& b, int nb, hipStream_t st);
 hipError_t launch_down_mfma(const BatchArgs& b, int nb, hipStream_t st);
+// The matrix-core tile kernels (decode_tile.hip): gate/up of a batch at any
+// group and 2 or 4 bits (t from launch_lora_a_tile: 1 or kLoraSlices slices
+// of partial sums [slices][nb][M][2r]; the linear launch sets the first clear_t
+// floats of b.t to zero),
+// and any linear [d][f] of a batch (the down weights on b.h), 1..16 tokens.
+// tile_linear_slices: 0 where the shape does not fit, else the slices of k;
+// with more than one, scratch holds tile_scratch_bytes, and the gate/up launch
+// before it (given the same scratch) clears its counters.
+bool tile_gateup_supported(int M, int d, int f, int g, int bits, int r, int nb);
+int tile_linear_slices(int M, int n, int k, int g, int bits, int nb);
+size_t tile_scratch_bytes(int sk, int nb, int M, int n);
+hipError_t launch_lora_a_tile(const BatchArgs& b, int nb, int slices, hipStream_t st);
+hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scratch, hipStream_t st);
+hipError_t launch_linear_tile(const BatchArgs& b, int nb, int clear_t, float* scratch, hipStream_t st);
 hipError_t launch_gateup_batch(const BatchArgs& b, int nb, hipStream_t st);
 hipError_t launch_down_batch(const BatchArgs& b, int nb, hipStream_t st);
 // y[m] = sum_j w[m k + j] * yi[m k + j] over the k routed experts of token m

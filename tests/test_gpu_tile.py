@@ -1,0 +1,133 @@
+"""The matrix-core tile kernels at several tokens, against the oracle: every
+group and width they take, rows that are no whole number of steps, K slices,
+tiles side by side, batches whose ranges straddle blocks, and each adapter
+rank.  Bars as for the other decode paths: y and h are binary16, sums fp32."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+import workloads as wl
+from qmlp_testutil import act_tensor, values_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    import paper_2606_04238_amd as q
+    return q
+
+
+def _pack(q, W, bits, g):
+    return {2: q.pack_w2, 3: q.pack_w3, 4: q.pack_w4}[bits](torch.from_numpy(W).cuda(), g)
+
+
+def _block(q, cfg, l, gb, gg, db, dg):
+    L = wl.layer(cfg, l)
+    lo = (L.A_gate, L.B_gate, L.A_up, L.B_up) if cfg.r else (None,) * 4
+    m = q.MLP(_pack(q, L.W_gate, gb, gg), _pack(q, L.W_up, gb, gg), _pack(q, L.W_down, db, dg),
+              *(act_tensor(t) if t is not None else None for t in lo), lora_scale=0.75)
+
+    def ref(x):
+        return orc.forward(orc.quantize(L.W_gate, gb, gg), orc.quantize(L.W_up, gb, gg),
+                           orc.quantize(L.W_down, db, dg), *lo, x, lora_scale=0.75)
+    return m, L.x, ref
+
+
+SHAPES = [  # d, f, gate bits, group, down bits, group, rank
+    (512, 1024, 2, 64, 4, 64, 8),          # one step per row: tiles side by side
+    (2880, 2880, 2, 64, 4, 64, 16),        # ragged last steps (d and f)
+    (2560, 1280, 2, 32, 4, 128, 16),       # 2-bit group 32
+    (1344, 448, 2, 32, 4, 32, 32),         # ragged, 4-bit group 32
+    (4160, 640, 2, 64, 4, 128, 32),        # nine steps: gate and up in turn
+    (2304, 6656, 4, 128, 4, 128, 0),       # uniform 4 bits, two K slices, no adapters
+    (1152, 7040, 4, 32, 2, 128, 16),       # 4-bit group 32 gate/up, 2-bit down in two slices
+    (640, 13312, 2, 128, 2, 64, 8),        # three K slices at 2 bits
+    (1280, 3200, 3, 32, 4, 64, 8),         # 3-bit gate/up (stand-alone) with a tile down
+]
+
+
+@pytest.mark.parametrize("M", [2, 3, 5, 8, 16])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_forward_matches_oracle(q, shape, M):
+    d, f, gb, gg, db, dg, r = shape
+    print("tile forward", shape, "M", M, flush=True)
+    cfg = wl.Config("tile", M=M, d=d, f=f, g=gg, r=r, L=1)
+    m, xb, ref = _block(q, cfg, 0, gb, gg, db, dg)
+    x = act_tensor(xb)
+    ws = q.workspace(m, M)
+    y = q.forward(m, x, ws=ws)
+    want = ref(xb)
+    torch.cuda.synchronize()
+    assert orc.max_rel_err(values_of(y), want) <= 1e-2
+    assert float(np.linalg.norm(values_of(y) - want) / np.linalg.norm(want)) <= 1.2e-3
+    again = q.forward(m, x, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(again, y)
+
+
+@pytest.mark.parametrize("L", [2, 7, 43])
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[3], SHAPES[7]])
+def test_layers_match_blocks(q, shape, L):
+    """A batch (ranges that straddle blocks, two batches at 43) against the
+    oracle on sampled blocks and each block's own call on all of them."""
+    d, f, gb, gg, db, dg, r = shape
+    M = 6
+    print("tile layers", shape, "L", L, flush=True)
+    cfg = wl.Config("tile", M=M, d=d, f=f, g=gg, r=r, L=L)
+    blocks = [_block(q, cfg, l, gb, gg, db, dg) for l in range(min(L, 3))]
+    layers = q.Layers([blocks[l % len(blocks)][0] for l in range(L)])
+    rng = np.random.default_rng(3)
+    xb = rng.standard_normal((L, M, d)).astype(np.float16)
+    x = torch.from_numpy(xb).cuda()
+    ws = q.layers_workspace(layers, M)
+    y = q.forward_layers(layers, x, ws=ws)
+    torch.cuda.synchronize()
+    for l in sorted({0, L // 2, L - 1}):
+        want = blocks[l % len(blocks)][2](xb[l].view(np.uint16))
+        assert orc.max_rel_err(values_of(y[l]), want) <= 1e-2
+    for l in range(L):
+        one = q.forward(layers.mlps[l], x[l])
+        assert orc.max_rel_err(values_of(y[l]), values_of(one)) <= 2e-3
+    assert torch.equal(q.forward_layers(layers, x, ws=ws), y)
+
+
+@pytest.mark.parametrize("M", [2, 9, 16])
+@pytest.mark.parametrize("n,k,bits,g,L", [(64, 64, 4, 64, 1), (192, 320, 4, 32, 3), (1088, 2560, 4, 128, 5),
+                                          (320, 4096, 2, 64, 2), (17408, 1024, 4, 128, 1), (128, 6144, 4, 64, 40)])
+def test_linear_matches_oracle(q, n, k, bits, g, L, M):
+    print("tile linear", n, k, bits, g, "L", L, "M", M, flush=True)
+    rng = np.random.default_rng([n, k, M])
+    Ws = [(0.02 * rng.standard_normal((n, k))).astype(np.float32) for _ in range(min(L, 2))]
+    xb = rng.standard_normal((L, M, k)).astype(np.float16)
+    qs = [_pack(q, W, bits, g) for W in Ws]
+    y = q.linear_batch([qs[l % len(qs)] for l in range(L)], torch.from_numpy(xb).cuda())
+    torch.cuda.synchronize()
+    for l in sorted({0, L // 2, L - 1}):
+        want = orc.down(orc.quantize(Ws[l % len(Ws)], bits, g), xb[l].astype(np.float64))
+        assert orc.max_rel_err(values_of(y[l]), want) <= 2e-3
+
+
+@pytest.mark.parametrize("M", [9, 16])
+def test_slices_leave_the_workspace_clean(q, M):
+    """Two slices of f: past t and h the workspace is zero after a call, so a
+    workspace that serves other token counts (the one-kernel layer's hand-off
+    words) never meets stale partial sums; and it does serve them."""
+    cfg = wl.Config("tile_ws", M=M, d=1024, f=6656, g=128, r=16, L=1)
+    print("tile workspace", M, flush=True)
+    m, xb, ref = _block(q, cfg, 0, 2, 128, 4, 128)
+    ws = q.workspace(m, M)
+    want = ref(xb)
+    r256 = lambda v: (v + 255) // 256 * 256
+    head = 1024 + r256(M * 2 * cfg.r * 4) + r256(M * cfg.f * 2)
+    for _ in range(2):
+        y = q.forward(m, act_tensor(xb), ws=ws)
+        torch.cuda.synchronize()
+        assert orc.max_rel_err(values_of(y), want) <= 1e-2
+        assert not bool(ws[head:].any())
+    for k in (1, M, 4, 2, M):
+        y = q.forward(m, act_tensor(xb[:k]), ws=ws)
+        torch.cuda.synchronize()
+        assert q.workspace_errors(ws) == 0
+        assert orc.max_rel_err(values_of(y), want[:k]) <= 1e-2
