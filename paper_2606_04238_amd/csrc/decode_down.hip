@@ -97,6 +97,43 @@ hipError_t launch_moe_combine(const uint16_t* yi, const float* w, int M, int k, 
     return hipGetLastError();
 }
 
+// The same over the tile kernels' fp32 outputs yi [S][M k][d] (S slices of
+// each instance's sum, added in order): nothing is rounded before the sum.
+// Four outputs per thread (d % 16 == 0).
+__global__ void __launch_bounds__(256)
+moe_combine_f32_kernel(const float* __restrict__ yi, const float* __restrict__ w, int M, int k, int d, int S,
+                       uint16_t* __restrict__ y, unsigned* ctl) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i == 0 && blockIdx.y == 0 && ctl)
+        advance_call_counter(ctl + kMoeCtlEpoch);
+    const int m = blockIdx.y, c = 4 * i;
+    if (c >= d)
+        return;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < k; ++j) {
+        const float wj = w[m * k + j];
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < S; ++s) {
+            const float4 p = *reinterpret_cast<const float4*>(yi + ((long)s * M * k + m * k + j) * d + c);
+            v[0] += p.x;
+            v[1] += p.y;
+            v[2] += p.z;
+            v[3] += p.w;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u] += wj * v[u];
+    }
+    *reinterpret_cast<uint2*>(y + (long)m * d + c) =
+        make_uint2(f2h(acc[0]) | (f2h(acc[1]) << 16), f2h(acc[2]) | (f2h(acc[3]) << 16));
+}
+
+hipError_t launch_moe_combine_f32(const float* yi, const float* w, int M, int k, int d, int S, uint16_t* y,
+                                  unsigned* ctl, hipStream_t st) {
+    moe_combine_f32_kernel<<<dim3((unsigned)((d / 4 + 255) / 256), (unsigned)M), 256, 0, st>>>(yi, w, M, k, d, S, y,
+                                                                                               ctl);
+    return hipGetLastError();
+}
+
 bool down_combine_fits(const BatchArgs& b, int nb) {
     return b.route && b.M == 1 && b.xdiv >= 1 && nb % b.xdiv == 0 && (b.bd == 4 || (b.bd == 2 && b.gd != 32)) &&
            down_combine_fits_shape(b.d, b.f, b.xdiv, b.bd);

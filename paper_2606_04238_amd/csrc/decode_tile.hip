@@ -358,6 +358,50 @@ __device__ __forceinline__ void tile_step(TileW<B, G>& w, const AOps<B, G>& a, c
     }
 }
 
+// ---- routed batches (mixture of experts): instance i (token i / xdiv) runs
+// expert route[i].  The "blocks" the workgroups walk are the experts that have
+// instances, so an expert several tokens share is read once; its instances
+// are the operand's 16 rows (an expert of more than 16 counts once per 16).
+// Every wave works it out from the ids, one instance per lane.
+struct Routed {
+    int e;                   // expert of a block
+    unsigned long long mask; // its instances
+};
+__device__ __forceinline__ int route_id(const BatchArgs& b, int n, int lane) {
+    int id = lane < n ? b.route[lane] : -1;
+    if (lane < n)
+        id = id < 0 ? 0 : (id >= b.nexp ? b.nexp - 1 : id);
+    return id;
+}
+__device__ __forceinline__ int route_blocks(const BatchArgs& b, int id) {
+    int nv = 0;
+    for (int e = 0; e < b.nexp; ++e) nv += (__popcll(__ballot(id == e)) + 15) >> 4;
+    return nv;
+}
+__device__ __forceinline__ Routed route_block(const BatchArgs& b, int id, int l) {
+    Routed r{0, 0ull};
+    for (int e = 0; e < b.nexp; ++e) {
+        const unsigned long long mask = __ballot(id == e);
+        const int c = (__popcll(mask) + 15) >> 4;
+        if (l < c) {
+            r.e = e;
+            r.mask = mask;
+            for (int i = 0; i < 16 * l; ++i) r.mask &= r.mask - 1;
+            break;
+        }
+        l -= c;
+    }
+    return r;
+}
+// The j-th instance of the mask (j < 16); the first where it has fewer.
+__device__ __forceinline__ int route_row(unsigned long long mask, int j) {
+    int row = __builtin_ctzll(mask);
+    for (int i = 0; i < 16 && mask; ++i, mask &= mask - 1)
+        if (i == j)
+            row = __builtin_ctzll(mask);
+    return row;
+}
+
 constexpr int kTileCounters = 256;                // words at the start of the scratch
 
 struct TilePlan {
@@ -366,7 +410,8 @@ struct TilePlan {
     int tg;                  // tiles of a tile lane per barrier
     int sk, ns;              // K slices, steps of a row
     int wgs;                 // workgroups per K slice
-    int tq, tr;              // tiles of the batch over workgroups: quotient, remainder
+    int wpb;                 // workgroups per block, 0: every workgroup its share of the whole batch
+    int tq, tr;              // tiles (of a block, of the batch) over those workgroups: quotient, remainder
     int sq, sr;              // steps of a row over slices
     int ipw, ikw;            // 2^16 / waves of a tile lane and / kw, rounded up (waves are below 16)
     int pack;                // packed steps
@@ -388,16 +433,18 @@ struct TilePlan {
 // it, into sums of their own, of which the rows of the other step are
 // dropped; unit u takes the wave's even (u & 1 = 0) or odd steps of a tile.
 // A Qwen3-8B-shaped down half (48 steps) then needs no second slice.
+// RT: a routed batch of nb instances of one token each (above); h [nb][f], and
+// the linear leaves fp32 [sk][nb][N] in scratch for the combine.
 // NSET register sets: NSET - 1 units
 // (the SPW steps of one matrix of one tile) are in flight per wave.
-template <int B, int G, bool GU, int MS, int SPW, bool PACK, int NW, int NSET>
+template <int B, int G, bool GU, int MS, int SPW, bool PACK, bool RT, int NW, int NSET>
 __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, TilePlan p, float* scratch) {
     typedef Lay<B, G> Y;
     static_assert(NSET % MS == 0, "a set holds one matrix or parity");
     static_assert(!PACK || (!GU && MS == 2), "packed steps: linear only");
     constexpr int SK2 = PACK ? 2 : 1;                      // K steps per operand
     constexpr int NM = GU ? 2 : 1;
-    const int K = GU ? b.d : b.f, N = GU ? b.f : b.d, M = b.M;
+    const int K = GU ? b.d : b.f, N = GU ? b.f : b.d;
     const int r = GU ? b.r : 0;
     const int tid = threadIdx.x, lane = tid & 63, qt = lane >> 4, jj = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -415,8 +462,23 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
     const int gs0 = sbeg + kw * SPW * SK2;                 // this wave's first step
     const int rb = K * B / 8, ng = K / G;
     const int tpb = N / 16;
-    const int t0 = wg * p.tq + min(wg, p.tr), t1 = t0 + p.tq + (wg < p.tr ? 1 : 0);
-    int l = nb == 1 ? 0 : (unsigned)t0 / (unsigned)tpb;
+    const int id = RT ? route_id(b, nb, lane) : 0;
+    const int total = RT ? route_blocks(b, id) * tpb : 0;
+    // This workgroup's tiles [t0, t1): of a block's, over p.wpb workgroups of its own, or an even share of
+    // the whole batch's.
+    int l, t0, t1;
+    if (!RT && p.wpb > 0) {
+        l = (unsigned)wg / (unsigned)p.wpb;
+        const int i = wg - l * p.wpb;
+        t0 = l * tpb + i * p.tq + min(i, p.tr);
+        t1 = t0 + p.tq + (i < p.tr ? 1 : 0);
+    } else {
+        const int tq = RT ? (int)((unsigned)total / (unsigned)p.wgs) : p.tq, tr = RT ? total - tq * p.wgs : p.tr;
+        t0 = wg * tq + min(wg, tr);
+        t1 = t0 + tq + (wg < tr ? 1 : 0);
+        l = nb == 1 ? 0 : (unsigned)t0 / (unsigned)tpb;
+    }
+    __shared__ int rows[2][16];                            // RT: instances of a block's operand rows
     KBatchM* kb = kbm();
     uint32_t ol[SPW * SK2];                                // lane's offsets of the code loads
 #pragma unroll
@@ -425,22 +487,28 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
         ol[st] = gs0 + st < send && 16 * u < rb ? (uint32_t)((lane & 7) * rb + 16 * u) : kPastEnd;
     }
     const uint32_t ml = (uint32_t)(jj * ng + gs0 * Y::GSU + meta_first<Y::GSU>(qt)) * 4u;
-    float* part = scratch + kTileCounters;
-    if (GU && scratch && wg == 0) {
+    float* part = scratch + (RT ? 0 : kTileCounters);
+    if (!RT && GU && scratch && wg == 0) {
         for (int i = tid; i < kTileCounters; i += p.threads) reinterpret_cast<uint32_t*>(scratch)[i] = 0u;
     }
-    if (!GU && wg == 0 && sl == 0)
+    if (!RT && !GU && wg == 0 && sl == 0)
         for (int i = tid; i < p.ts; i += p.threads) b.t[i] = 0.0f;
     int buf = 0, fin = 0, par = 0;                         // LDS buffer and adding wave of the next tiles
 
     for (int seg = t0; seg < t1; ++l) {
         const int tend = (l + 1) * tpb < t1 ? (l + 1) * tpb : t1;
         const int n = (tend - seg + TW - 1) / TW;          // uniform over the workgroup
+        const Routed rt = RT ? route_block(b, id, l) : Routed{l, 0ull};
+        const int e = rt.e;
+        const int M = RT ? min(__popcll(rt.mask), 16) : b.M;     // operand rows in use
+        const int own = RT ? route_row(rt.mask, jj) : 0;   // instance of this lane's operand row
+        if (RT && wave == 0 && lane < 16)                  // read behind this segment's first barrier
+            rows[par][lane] = own;
         const uint32_t cbytes = (uint32_t)N * (uint32_t)rb, mbytes = (uint32_t)N * (uint32_t)ng * 4u;
-        const Rsrc rc0 = rsrc(!GU ? kb->lay[l].cd : mat ? kb->lay[l].cu : kb->lay[l].cg, cbytes);
-        const Rsrc rm0 = rsrc(!GU ? kb->lay[l].md : mat ? kb->lay[l].mu : kb->lay[l].mg, mbytes);
-        const Rsrc rc1 = GU && MS == 2 ? rsrc(kb->lay[l].cu, cbytes) : rc0;
-        const Rsrc rm1 = GU && MS == 2 ? rsrc(kb->lay[l].mu, mbytes) : rm0;
+        const Rsrc rc0 = rsrc(!GU ? kb->lay[e].cd : mat ? kb->lay[e].cu : kb->lay[e].cg, cbytes);
+        const Rsrc rm0 = rsrc(!GU ? kb->lay[e].md : mat ? kb->lay[e].mu : kb->lay[e].mg, mbytes);
+        const Rsrc rc1 = GU && MS == 2 ? rsrc(kb->lay[e].cu, cbytes) : rc0;
+        const Rsrc rm1 = GU && MS == 2 ? rsrc(kb->lay[e].mu, mbytes) : rm0;
         struct Set {
             TileW<B, G> w[SPW];
         };
@@ -457,15 +525,20 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
                              real ? row * (uint32_t)ng * 4u : kPastEnd);
             }
         };
-        // this block's activations and lora_scale t, ahead of the first weights
+        // This block's activations, ahead of the first weights: behind them they wait in the memory's queues
+        // (one Qwen3-8B-shaped down half: 14.0 us this way, 17.8 the other).
         AOps<B, G> a[SPW];
         {
             const int la = fresh(lane);
-            const Rsrc rx = rsrc((GU ? b.x : b.h) + (long)l * M * K, (uint32_t)M * (uint32_t)K * 2u);
+            const Rsrc rx = RT ? rsrc(GU ? b.x : b.h, (uint32_t)(GU ? nb / b.xdiv : nb) * (uint32_t)K * 2u)
+                               : rsrc((GU ? b.x : b.h) + (long)l * M * K, (uint32_t)M * (uint32_t)K * 2u);
 #pragma unroll
             for (int st = 0; st < SPW; ++st) {
                 const int gs = PACK ? gs0 + 2 * st + ((la >> 3) & 1) : gs0 + st;
-                act_load<B, G>(a[st], rx, gs, PACK ? la & 7 : la & 15, M, K, gs < send, la);
+                if constexpr (RT)
+                    act_load<B, G>(a[st], rx, gs, GU ? own / b.xdiv : own, nb, K, gs < send && (la & 15) < M, la);
+                else
+                    act_load<B, G>(a[st], rx, gs, PACK ? la & 7 : la & 15, M, K, gs < send, la);
             }
         }
         // LoRA-B of the tile this wave adds in the group of TG tiles from i on:
@@ -480,24 +553,36 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
                 const int la = fresh(lane);
                 const uint32_t o = real ? (uint32_t)((tile - l * tpb) * 16 * r + (la & 15) * r + (la >> 4) * (r / 4)) * 2u
                                         : kPastEnd;
-                lb[0] = bload16<0>(rsrc(kb->lay[l].Bg, bytes), o, 0);
-                lb[1] = bload16<0>(rsrc(kb->lay[l].Bu, bytes), o, 0);
+                lb[0] = bload16<0>(rsrc(kb->lay[e].Bg, bytes), o, 0);
+                lb[1] = bload16<0>(rsrc(kb->lay[e].Bu, bytes), o, 0);
             }
         };
-        if constexpr (GU) {
-            if (r > 0) {
-                // ts[m][u][16 q + j] = lora_scale t[token j][rank q r/4 + u], the slices of d in order; read
-                // behind this segment's first barrier
-                const float ls = kb->lay[l].lora_scale;
-                const int lg = r == 8 ? 1 : r == 16 ? 2 : 3;       // r / 4 = 2^lg
-                for (int i = fresh(tid); i < 2 * (r / 4) * 64; i += p.threads) {
-                    const int j = i & 15, q = (i >> 4) & 3, m = i >> (6 + lg), u = (i >> 6) - (m << lg);
-                    const float* tc = b.t + ((long)l * M + (j < M ? j : 0)) * 2 * r + m * r + q * (r / 4) + u;
-                    float v = tc[0];
-                    for (int sl = 1; sl < p.ts; ++sl) v += tc[(long)sl * nb * M * 2 * r];
-                    ts[par * 1024 + (m * 8 + u) * 64 + (i & 63)] = j < M ? ls * v : 0.0f;
-                }
-            }
+        // ts[m][u][16 q + j] = lora_scale t[token j][rank q r/4 + u], the slices of d in order; read behind
+        // this segment's first barrier.
+        const int lg = r == 8 ? 1 : r == 16 ? 2 : 3;       // r / 4 = 2^lg
+        const int nts = GU && r > 0 ? 2 * (r / 4) * 64 : 0;
+        auto t_load = [&](int i, float (&v)[kLoraSlices]) {
+            const int j = i & 15, q = (i >> 4) & 3, m = i >> (6 + lg), u = (i >> 6) - (m << lg);
+            const long row = RT ? own : (long)l * M + (j < M ? j : 0);     // i & 15 = lane & 15
+            const float* tc = b.t + row * 2 * r + m * r + q * (r / 4) + u;
+#pragma unroll
+            for (int sl = 0; sl < kLoraSlices; ++sl)
+                v[sl] = tc[(long)(sl < p.ts ? sl : 0) * nb * (RT ? 1 : M) * 2 * r];
+        };
+        auto t_store = [&](int i, const float (&v)[kLoraSlices]) {
+            const int j = i & 15, m = i >> (6 + lg), u = (i >> 6) - (m << lg);
+            float t = v[0];
+#pragma unroll
+            for (int sl = 1; sl < kLoraSlices; ++sl)
+                if (sl < p.ts)
+                    t += v[sl];
+            ts[par * 1024 + (m * 8 + u) * 64 + (i & 63)] = j < M ? kb->lay[e].lora_scale * t : 0.0f;
+        };
+        float tv[2][kLoraSlices];
+        if (nts > 0) {
+            const int i = fresh(tid);
+            t_load(i < nts ? i : 0, tv[0]);
+            t_load(i + p.threads < nts ? i + p.threads : 0, tv[1]);
         }
         Set S[NSET];
 #pragma unroll
@@ -508,6 +593,15 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
             act_mask<B, G>(a[st], PACK ? gs0 + 2 * st + ((lane >> 3) & 1) : gs0 + st, K, lane);
             act_convert<B, G>(a[st]);
             group_sums<B, G>(a[st], cr[st], lane);
+        }
+        if (nts > 0) {
+            const int i = fresh(tid);
+            if (i < nts) t_store(i, tv[0]);
+            if (i + p.threads < nts) t_store(i + p.threads, tv[1]);
+            for (int k = i + 2 * p.threads; k < nts; k += p.threads) {
+                t_load(k, tv[0]);
+                t_store(k, tv[0]);
+            }
         }
         lora_load(0);
         int g = 0;                                         // tile within its group
@@ -547,10 +641,12 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
                 for (int v = 0; v < 4; ++v) {
                     const int tok = 4 * (la >> 4) + v;
                     if (tok < M) {
-                        const long at = ((long)l * M + tok) * N + o;
+                        const long at = (RT ? (long)rows[par][tok] : (long)l * M + tok) * N + o;
                         if constexpr (GU) {
                             const float gv = acc[0][v];
                             b.h[at] = (uint16_t)f2h(gv / (1.0f + __expf(-gv)) * acc[1][v]);
+                        } else if (RT) {
+                            part[(long)sl * nb * N + at] = acc[0][v];
                         } else if (p.sk > 1) {
                             __hip_atomic_store(part + (long)sl * nb * M * N + at, acc[0][v], __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
@@ -605,7 +701,8 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
         seg = tend;
         par ^= 1;
     }
-    if constexpr (!GU) {
+    if constexpr (!GU && !RT) {
+        const int M = b.M;
         if (p.sk > 1) {
             // every partial of this workgroup is out, then the range's counter: the last slice adds them all
             __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -654,17 +751,24 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
 // launch adds the slices in order.  The launch is one trip to memory, so it
 // is spread over as many compute units as there is room for partials: one
 // Qwen3-8B-shaped block at M = 8 takes 4.5 us with four slices, 8.0 with one.
+// RT: a routed batch of nb instances, block l its l-th expert; t [S][nb][2r].
+template <bool RT>
 __global__ void __launch_bounds__(256) tile_lora_kernel(BatchArgs b, int nb, int S) {
     __shared__ f32x4_t red[4][64];
-    const int l = blockIdx.y, d = b.d, r = b.r, M = b.M;
-    const int tile = S == 1 ? blockIdx.x : blockIdx.x / kLoraSlices, s = blockIdx.x - tile * S;
+    const int d = b.d, r = b.r;
+    const int s = blockIdx.z, tile = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4;
+    const int id = RT ? route_id(b, nb, lane) : 0;
+    const Routed rt = RT ? route_block(b, id, blockIdx.y) : Routed{(int)blockIdx.y, 0ull};
+    if (RT && !rt.mask)
+        return;                                            // fewer experts than instances
+    const int l = rt.e, M = RT ? min(__popcll(rt.mask), 16) : b.M;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = tile * 16 + (lane & 15);                 // this lane's row of [A_g; A_u]
     const int all = d / 32, w = 4 * s + wave, s0 = w * all / (4 * S), n = (w + 1) * all / (4 * S) - s0;
     const uint16_t* ar = (c < r ? kbm()->lay[l].Ag + (long)c * d : kbm()->lay[l].Au + (long)(c - r) * d) + s0 * 32 + 8 * q;
     const int j = (lane & 15) < M ? (lane & 15) : 0;       // rows past M: token 0, dropped
-    const uint16_t* xr = b.x + ((long)l * M + j) * d + s0 * 32 + 8 * q;
+    const uint16_t* xr = b.x + (RT ? (long)(route_row(rt.mask, j) / b.xdiv) : (long)l * M + j) * d + s0 * 32 + 8 * q;
     f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
     constexpr int KC = 4;
     for (int i = 0; i < n; i += KC) {
@@ -687,12 +791,12 @@ __global__ void __launch_bounds__(256) tile_lora_kernel(BatchArgs b, int nb, int
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             if (4 * q + v < M)
-                b.t[(((long)s * nb + l) * M + 4 * q + v) * 2 * r + c] = t[v];
+                b.t[(RT ? (long)s * nb + route_row(rt.mask, 4 * q + v) : ((long)s * nb + l) * M + 4 * q + v) * 2 * r + c] = t[v];
     }
 }
 
 constexpr int kTileWaves = 12;                 // waves of a workgroup, 168 registers each
-constexpr size_t kTileLds = 160 * 1024;
+constexpr size_t kTileLds = 159 * 1024;          // beside the routed batch's row table
 
 int tile_cu_count() {
     static int cache[64];
@@ -745,6 +849,28 @@ bool tile_group(TilePlan& p, int nm, size_t more) {
     }
 }
 
+// Workgroups of their own for each block of a batch, or an even share of the
+// whole batch for every workgroup?  A workgroup that crosses into another block
+// stages new activations with no weights in flight, which measured 7 us, about
+// the time of kCross tiles; whole workgroups per block leave some compute units
+// without work or the largest share a tile longer.  Own workgroups against an
+// even share: 12 blocks of d = 2048, f = 6144 at M = 16 63 against 71 us, 20 of
+// d = f = 2880 69 against 74, 36 Qwen3-4B-shaped ones 227 against 230.
+void tile_blocks(TilePlan& p, int nb, int tpb, int cus) {
+    constexpr long kCross = 5;
+    p.wpb = 0;
+    const int per = cus / p.sk / nb < (tpb + p.tw - 1) / p.tw ? cus / p.sk / nb : (tpb + p.tw - 1) / p.tw;
+    if (nb == 1 || per < 1)
+        return;
+    const long all = (long)nb * tpb, shared = (all + p.wgs - 1) / p.wgs + kCross * p.tw;
+    if ((tpb + per - 1) / per <= shared) {
+        p.wpb = per;
+        p.wgs = per * nb;
+        p.tq = tpb / per;
+        p.tr = tpb % per;
+    }
+}
+
 // Gate/up: K = d.  Gate and up take waves of their own while both fit in one
 // workgroup (twice the waves share the stream of a short row), else every
 // wave takes a tile's gate, then its up.  Rows past kTileWaves steps do not
@@ -767,6 +893,7 @@ bool plan_gateup(int M, int d, int f, int g, int bits, int r, int nb, TilePlan& 
     p.threads = p.tw * p.kw * p.mw * 64;
     p.wgs = tile_wgs((long)nb * (f / 16), p.tw, 1, cus);
     tile_shares(p, (long)nb * (f / 16));
+    tile_blocks(p, nb, f / 16, cus);
     return tile_group(p, 2, r > 0 ? 8192 : 0);
 }
 
@@ -794,6 +921,7 @@ bool plan_linear(int M, int n, int k, int g, int bits, int nb, TilePlan& p) {
     p.threads = p.tw * p.kw * 64;
     p.wgs = tile_wgs((long)nb * (n / 16), p.tw, p.sk, cus);
     tile_shares(p, (long)nb * (n / 16));
+    tile_blocks(p, nb, n / 16, cus);
     return tile_group(p, 1, 0);
 }
 
@@ -822,9 +950,13 @@ static hipError_t tile_run(KERNEL k, const BatchArgs& b, int nb, const TilePlan&
 }
 
 hipError_t launch_lora_a_tile(const BatchArgs& b, int nb, int slices, hipStream_t st) {
-    if ((slices != 1 && slices != kLoraSlices) || b.M < 1 || b.M > 16 || nb < 1 || nb > kBatchMax || b.d % 64 != 0 || (b.r != 8 && b.r != 16 && b.r != 32))
+    if (slices < 1 || slices > kLoraSlices || b.M < 1 || b.M > 16 || nb < 1 || nb > kBatchMax || b.d % 64 != 0 || (b.r != 8 && b.r != 16 && b.r != 32))
         return hipErrorInvalidValue;
-    tile_lora_kernel<<<dim3((unsigned)(2 * b.r / 16 * slices), (unsigned)nb), 256, 0, st>>>(b, nb, slices);
+    const dim3 grid((unsigned)(2 * b.r / 16), (unsigned)nb, (unsigned)slices);
+    if (b.route)
+        tile_lora_kernel<true><<<grid, 256, 0, st>>>(b, nb, slices);
+    else
+        tile_lora_kernel<false><<<grid, 256, 0, st>>>(b, nb, slices);
     return hipGetLastError();
 }
 
@@ -833,23 +965,26 @@ hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scr
     if (!plan_gateup(b.M, b.d, b.f, b.gg, b.bg, b.r, nb, p))
         return hipErrorInvalidValue;
     p.ts = slices;
-#define QMLP_TGU(B_, G_)                                                                  \
-    if (b.bg == B_ && b.gg == G_)                                                         \
-        return p.mw == 2 ? tile_run(tile_kernel<B_, G_, true, 1, 1, false, kTileWaves, 4>, b, nb, p, scratch, st) \
-                         : tile_run(tile_kernel<B_, G_, true, 2, 1, false, kTileWaves, 4>, b, nb, p, scratch, st);
+#define QMLP_TGU_R(B_, G_, R_)                                                            \
+    if (b.bg == B_ && b.gg == G_ && (b.route != nullptr) == R_)                           \
+        return p.mw == 2 ? tile_run(tile_kernel<B_, G_, true, 1, 1, false, R_, kTileWaves, 4>, b, nb, p, scratch, st) \
+                         : tile_run(tile_kernel<B_, G_, true, 2, 1, false, R_, kTileWaves, 4>, b, nb, p, scratch, st);
+#define QMLP_TGU(B_, G_) QMLP_TGU_R(B_, G_, false) QMLP_TGU_R(B_, G_, true)
     QMLP_TGU(2, 128) QMLP_TGU(2, 64) QMLP_TGU(2, 32) QMLP_TGU(4, 128) QMLP_TGU(4, 64) QMLP_TGU(4, 32)
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_linear_tile(const BatchArgs& b, int nb, int clear_t, float* scratch, hipStream_t st) {
     TilePlan p;
-    if (!plan_linear(b.M, b.d, b.f, b.gd, b.bd, nb, p) || (p.sk > 1 && !scratch))
+    // a routed batch: up to 16 operand rows, partials always
+    if (!plan_linear(b.route ? 16 : b.M, b.d, b.f, b.gd, b.bd, nb, p) || ((p.sk > 1 || b.route) && !scratch))
         return hipErrorInvalidValue;
     p.ts = clear_t;
 #define QMLP_TLN(B_, G_, S_)                                                              \
     if (b.bd == B_ && b.gd == G_)                                                         \
-        return p.pack ? tile_run(tile_kernel<B_, G_, false, 2, S_, true, kTileWaves, 2>, b, nb, p, scratch, st) \
-                      : tile_run(tile_kernel<B_, G_, false, 1, S_, false, kTileWaves, 3>, b, nb, p, scratch, st);
+        return b.route ? tile_run(tile_kernel<B_, G_, false, 1, S_, false, true, kTileWaves, 3>, b, nb, p, scratch, st) \
+               : p.pack ? tile_run(tile_kernel<B_, G_, false, 2, S_, true, false, kTileWaves, 2>, b, nb, p, scratch, st) \
+                        : tile_run(tile_kernel<B_, G_, false, 1, S_, false, false, kTileWaves, 3>, b, nb, p, scratch, st);
     QMLP_TLN(4, 128, 2) QMLP_TLN(4, 64, 2) QMLP_TLN(4, 32, 1) QMLP_TLN(2, 128, 1) QMLP_TLN(2, 64, 1)
     return hipErrorInvalidValue;
 }

@@ -180,6 +180,8 @@ hipError_t launch_down_mfma(const BatchArgs& b, int nb, hipStream_t st);
 // tile_linear_slices: 0 where the shape does not fit, else the slices of k;
 // with more than one, scratch holds tile_scratch_bytes, and the gate/up launch
 // before it (given the same scratch) clears its counters.
+// A routed batch (b.route) of nb one-token instances: experts that several
+// tokens share are read once; the linear leaves fp32 [slices][nb][d] in scratch.
 bool tile_gateup_supported(int M, int d, int f, int g, int bits, int r, int nb);
 int tile_linear_slices(int M, int n, int k, int g, int bits, int nb);
 size_t tile_scratch_bytes(int sk, int nb, int M, int n);
@@ -194,6 +196,9 @@ hipError_t launch_down_batch(const BatchArgs& b, int nb, hipStream_t st);
 // advances.
 hipError_t launch_moe_combine(const uint16_t* yi, const float* w, int M, int k, int d, uint16_t* y,
                               unsigned* ctl, hipStream_t st);
+// ... over fp32 outputs yi [S][M k][d] of the tile kernels.
+hipError_t launch_moe_combine_f32(const float* yi, const float* w, int M, int k, int d, int S, uint16_t* y,
+                                  unsigned* ctl, hipStream_t st);
 size_t stack_ws_bytes(int d, int f, int r);
 int stack_max_layers();
 // Byte offset of the persistent stack launch's sticky error word in its area.

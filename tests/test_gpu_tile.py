@@ -131,3 +131,34 @@ def test_slices_leave_the_workspace_clean(q, M):
         torch.cuda.synchronize()
         assert q.workspace_errors(ws) == 0
         assert orc.max_rel_err(values_of(y), want[:k]) <= 1e-2
+
+
+@pytest.mark.parametrize("d,f,gb,g,db,r,E,k,M,same", [
+    (2048, 1600, 2, 64, 4, 16, 4, 4, 10, False),       # every expert shared by all tokens
+    (1600, 2048, 2, 64, 4, 32, 5, 4, 10, True),        # all forty instances on one expert: three operands of rows
+    (512, 6656, 2, 128, 4, 8, 6, 6, 6, False),         # two slices of f
+    (2560, 1024, 4, 128, 4, 0, 4, 2, 16, False),       # uniform 4 bits, no adapters
+])
+def test_shared_experts_match_oracle(q, d, f, gb, g, db, r, E, k, M, same):
+    """Routed layers whose experts are shared by enough tokens to run on the
+    tile kernels (each expert in use read once)."""
+    print("tile moe", d, f, E, k, M, flush=True)
+    cfg = wl.Config("tile_moe", M=1, d=d, f=f, g=g, r=r, L=1)
+    lays = [wl.layer(cfg, e) for e in range(E)]
+    mlps = [_block(q, cfg, e, gb, g, db, g)[0] for e in range(E)]
+    experts = q.Layers(mlps)
+    x = wl.activations(cfg, 9, 0, M=M)
+    idx, w = wl.routing(M, E, k, 1)
+    if same:
+        idx[:] = E - 2
+    ws = torch.zeros(q.moe_workspace_bytes(experts, M, k), dtype=torch.uint8, device="cuda")
+    assert ws.numel() > M * k * d * 4                  # fp32 outputs: the tile kernels run
+    ys = [q.forward_moe(experts, act_tensor(x), torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda(), ws=ws)
+          for _ in range(2)]
+    torch.cuda.synchronize()
+    oq = [(orc.quantize(l.W_gate, gb, g), orc.quantize(l.W_up, gb, g), orc.quantize(l.W_down, db, g)) +
+          ((l.A_gate, l.B_gate, l.A_up, l.B_up) if r else (None,) * 4) for l in lays]
+    want = orc.moe_forward(oq, idx, w, x, lora_scale=0.75)
+    assert orc.max_rel_err(values_of(ys[0]), want) <= 1e-2
+    assert torch.equal(ys[0], ys[1])
+    assert q.workspace_errors(ws) == 0 and int(ws[0:4].view(torch.int32).item()) == 2
