@@ -97,27 +97,41 @@ bool fused_mlp(const qmlp_mlp* mlp, int M) {
            fused_supported(M, mlp->gate.k_in, mlp->gate.n_out, mlp->gate.group, mlp->rank);
 }
 
-// Fewest tokens at which a half runs on the matrix-core tile kernels
-// (decode_tile.hip) instead of the stand-alone ones.
-constexpr int kTileMinTokens = 2;
+// Which halves run on the matrix-core tile kernels (decode_tile.hip) instead
+// of the stand-alone ones: from two tokens on every one that fits.  At one
+// token the stand-alone kernels' arithmetic still fits beside the weight
+// stream and they start sooner, so only large batches gain (kTileOneToken
+// weights per matrix; four blocks of d = 2560, f = 9728 lost, 45 against 49 us),
+// and of those (us, stand-alone and tile):
+//   gate/up in groups of 64 or more of long rows: 36 blocks of d = 2560, 4 bits
+//     299 and 271, 2 bits 214 and 202, 12 of d = 4608 116 and 107 (20 of d =
+//     2880 65 and 65; 4 bits in groups of 32 300 and 331, 2 bits 259 and 312);
+//   down of long rows, where a workgroup stages all of h for few rows: 36 blocks
+//     of f = 9728 (2-bit group-32 gate/up) 254 and 233, 20 of f = 17408 619 and
+//     500 (f = 2880 65 and 68).
+constexpr long kTileOneToken = 150000000;
 
 // Whether the gate/up half of a batch of nb such blocks takes the tile
 // kernels, and the slices of f its down half takes there (0: stand-alone).
 bool tile_gateup(const qmlp_mlp* mlp, int M, int nb) {
-    return M >= kTileMinTokens && tile_gateup_supported(M, mlp->gate.k_in, mlp->gate.n_out, mlp->gate.group,
-                                                        mlp->gate.bits, mlp->rank, nb);
+    const qmlp_qweight& w = mlp->gate;
+    if (M == 1 && ((long)nb * w.n_out * w.k_in < kTileOneToken || w.group < 64 || w.k_in < 2048))
+        return false;
+    return tile_gateup_supported(M, w.k_in, w.n_out, w.group, w.bits, mlp->rank, nb);
 }
 int tile_slices(const qmlp_qweight* w, int M, int nb) {
-    return M >= kTileMinTokens ? tile_linear_slices(M, w->n_out, w->k_in, w->group, w->bits, nb) : 0;
+    if (M == 1 && ((long)nb * w->n_out * w->k_in < kTileOneToken || w->k_in < 6144))
+        return 0;
+    return tile_linear_slices(M, w->n_out, w->k_in, w->group, w->bits, nb);
 }
 
 // Workspace: [control words, 1 KB][t: fp32][h: M x f activation type]
 // [T: M x 2r bfloat16, prefill only][t64: one [4][64] copy of tagged words
 // per block of the one-kernel layer, h32: 4 x f tagged words -- decode only,
 // that kernel's hand-offs; where the block runs on the tile kernels instead,
-// the same bytes hold the down slices' counters and partial sums, zero again after the call].  t is
-// M x 2r on the decode path and S x M x 2r split-K partials on the prefill
-// path.
+// the same bytes hold LoRA-A's slices and the down slices' counters and
+// partial sums, zero again after the call].  t is M x 2r on the decode path
+// and S x M x 2r split-K partials on the prefill path.
 constexpr size_t kCtlBytes = 1024;
 
 struct Workspace {
@@ -928,7 +942,7 @@ qmlp_status qmlp_linear_batch(const qmlp_qweight* w, int L, const void* x, int M
     b.f = k;
     b.gd = w[0].group;
     b.bd = bits;
-    return from_hip(tile_slices(&w[0], M, L) == 1 ? launch_linear_tile(b, L, 0, nullptr, static_cast<hipStream_t>(stream))
+    return from_hip(M > 1 && tile_slices(&w[0], M, L) == 1 ? launch_linear_tile(b, L, 0, nullptr, static_cast<hipStream_t>(stream))
                                                   : launch_down_batch(b, L, static_cast<hipStream_t>(stream)));
 }
 

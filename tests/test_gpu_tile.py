@@ -93,6 +93,32 @@ def test_layers_match_blocks(q, shape, L):
     assert torch.equal(q.forward_layers(layers, x, ws=ws), y)
 
 
+@pytest.mark.parametrize("L,shape", [
+    (12, (2048, 6144, 4, 128, 2, 64, 16)),    # whole steps, one K slice
+    (9, (2880, 6272, 2, 64, 4, 64, 8)),       # ragged rows, two K slices
+    (12, (2112, 6272, 4, 64, 2, 128, 0)),     # ragged rows, no adapters
+])
+def test_one_token_batches_match_blocks(q, L, shape):
+    """Large one-token batches (1.5e8 weights per matrix and more) take the
+    tile kernels, a block alone and a batch one block short do not."""
+    d, f, gb, gg, db, dg, r = shape
+    print("tile one token", shape, "L", L, flush=True)
+    assert L * d * f >= 150000000 > (L - 1) * d * f
+    cfg = wl.Config("tile", M=1, d=d, f=f, g=gg, r=r, L=2)
+    blocks = [_block(q, cfg, l, gb, gg, db, dg) for l in range(2)]
+    x = torch.from_numpy(np.random.default_rng(4).standard_normal((L, 1, d)).astype(np.float16)).cuda()
+    layers = q.Layers([blocks[l % 2][0] for l in range(L)])
+    ws = q.layers_workspace(layers, 1)
+    y = q.forward_layers(layers, x, ws=ws)
+    for l in (0, L - 1):
+        want = blocks[l % 2][2](x[l].cpu().numpy().view(np.uint16))
+        assert orc.max_rel_err(values_of(y[l]), want) <= 1e-2
+    short = q.forward_layers(q.Layers([blocks[l % 2][0] for l in range(L - 1)]), x[:L - 1].contiguous())
+    for l in range(L - 1):
+        assert orc.max_rel_err(values_of(y[l]), values_of(short[l])) <= 2e-3
+    assert torch.equal(q.forward_layers(layers, x, ws=ws), y)
+
+
 @pytest.mark.parametrize("M", [2, 9, 16])
 @pytest.mark.parametrize("n,k,bits,g,L", [(64, 64, 4, 64, 1), (192, 320, 4, 32, 3), (1088, 2560, 4, 128, 5),
                                           (320, 4096, 2, 64, 2), (17408, 1024, 4, 128, 1), (128, 6144, 4, 64, 40)])
