@@ -460,17 +460,25 @@ bool layers_batched(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
 enum class BatchPath { kBatched, kStreamed, kMfma, kTile };
 
 // The tile kernels come before those of decode_mfma.hip where they take both
-// halves: 36 Qwen3-8B-shaped blocks at M = 4 and 16 measured 401 and 457
-// against 476 and 520 us, two Qwen3-4B-shaped ones at M = 4 41 against 63 us,
-// three 14B-class ones at M = 8 104 against 190 us (40 of them at M = 16: 1006
-// against 988).  Rows too long for them stay there.
+// halves (us, those and these): 36 Qwen3-8B-shaped blocks at M = 4 and 16 450
+// and 403, 508 and 469, in groups of 64 at M = 8 541 and 473; ten 14B-class ones
+// (d = 5120, f = 17408, groups of 64) at M = 8 320 and 276, 40 in groups of 128
+// 888 and 871.  Only where the start-up no longer counts, a tile's gate and up
+// run in turn over more than eight steps, down runs in slices and groups of 64
+// double the corrections, do those stay ahead: 20 such 14B-class blocks 524 and
+// 528, 40 of them 969 and 986, at M = 4 936 and 970.  Rows too long for the tile
+// kernels stay there as well.
+constexpr long kMfmaWeights = 1800000000;
 BatchPath batch_path(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
     const int n = L < kBatchMax ? L : kBatchMax;
     if (layers_streamed(layers, L, M, dtype))
         return BatchPath::kStreamed;
-    if (layers_mfma(layers, L, M, dtype) && !(tile_gateup(layers, M, n) && tile_slices(&layers[0].down, M, n) > 0))
-        return BatchPath::kMfma;
-    return BatchPath::kTile;
+    if (!layers_mfma(layers, L, M, dtype))
+        return BatchPath::kTile;
+    const qmlp_qweight& w = layers[0].gate;
+    const int sk = tile_slices(&layers[0].down, M, n);
+    const bool late = w.group == 64 && w.k_in > 8 * 512 && sk > 1 && (long)n * w.n_out * w.k_in >= kMfmaWeights;
+    return tile_gateup(layers, M, n) && sk > 0 && !late ? BatchPath::kTile : BatchPath::kMfma;
 }
 
 // t of a batch: [nb][M][2r] fp32, kLoraSlices such arrays of partial sums on

@@ -6,6 +6,12 @@
 //                    (Sec. 3.1 Eq. (1), Sec. 3.3, Sec. 4.2);
 //   down launch:     y_l = W4down h_l (Sec. 3.3).
 //
+// Taken for the batches whose rows the tile kernels (decode_tile.hip) do not
+// hold (gate/up rows past 6144 codes, or down rows past their slices), and for
+// large batches of long rows in groups of 64, where these are ahead (40 blocks
+// of d = 5120, f = 17408 at 8 tokens: 969 us here, 986 there; 36 of d = 4096,
+// f = 12288: 541 and 473).
+//
 // With M tokens a weight feeds M multiply-adds; on the vector ALU that is
 // M/2 dot2 operations per weight on top of its dequantization, more than the
 // weight stream allows from a few tokens on.  Here every weight is unpacked
