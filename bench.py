@@ -66,7 +66,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 # the kernel trace (profile summaries); the streamed gate/up launch also
 # computes LoRA-A
 STEP_KERNELS = {"streamed": "gu_stream_kernel|dn_stream_kernel",
-                "mfma": "mf_lora_kernel|mf_gu_kernel|mf_dn_kernel"}
+                "mfma": "tile_lora_kernel|tile_kernel<2|tile_kernel<4"}
 METRIC = BASE_METRIC = ("achieved HBM GB/s (% of MI355X peak) and µs per W4/W2-GateUp MLP "
                         "decode step")
 

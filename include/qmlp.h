@@ -276,23 +276,26 @@ int qmlp_stack_launches(const qmlp_mlp *layers, int L, int M, qmlp_dtype dtype);
  * Binary16 blocks run in batches of up to 40.  At M = 1 in the
  * W4/W2-GateUp form (2-bit gate/up, 4-bit down, groups 64/128, rank 0, 8,
  * 16 or 32) with d % 512 == 0, d <= 4096, f % 128 == 0, f <= 12288, a batch
- * STREAMS: the LoRA-A products of every block (one launch), then one
- * persistent gate/up launch and one persistent down launch, each workgroup
- * owning a contiguous range of the batch's rows flattened over blocks, so
- * no workgroup waits for another and h of every block passes through the
- * workspace between the two launches.  At 3 <= M <= 16 in the same form
- * (d % 512 == 0, f % 256 == 0, and the LDS limits qmlp_layers_path
- * reports) a batch runs on the MATRIX CORES: the LoRA-A launch (fp32
- * partial sums over four slices of d, added in slice order by the next
- * launch), then one persistent gate/up launch and one persistent down
- * launch that multiply every unpacked weight into all M tokens with
- * v_mfma_f32_16x16x32_f16.  Every other binary16 batch runs the
- * stand-alone kernels as qmlp_forward_batch does; bfloat16 runs
+ * STREAMS: one persistent gate/up launch that also computes the LoRA-A
+ * products and one persistent down launch, each workgroup owning a
+ * contiguous range of the batch's rows flattened over blocks; h of every
+ * block passes through the workspace between the two launches.  Every other
+ * binary16 batch of two tokens or more runs on the MATRIX CORES where its
+ * halves fit (gate/up at 2 or 4 bits with rows of at most twelve steps of
+ * 1024/bits codes; any down): the LoRA-A launch (fp32 partial sums over four
+ * slices of d, added in slice order by the next launch), then one gate/up
+ * launch and one down launch that multiply every unpacked weight into all M
+ * tokens with v_mfma_f32_16x16x32_f16; large batches of long rows do so at
+ * one token too.  A half that does not fit (3-bit gate/up) and the rest run
+ * the stand-alone kernels as qmlp_forward_batch does; bfloat16 runs
  * qmlp_forward once per block.
  *
  * ws/ws_bytes: at least qmlp_layers_workspace_bytes(layers, L, M, dtype)
  * (binary16: that of qmlp_forward_batch, with four times its t area on the
- * matrix cores and twice on the streamed path).  On the streamed path with
+ * matrix cores and twice on the streamed path, and on the matrix cores, where
+ * rows of down are longer than one workgroup holds -- f > 6144 at 4 bits,
+ * 12288 at up to eight tokens -- fp32 partial sums [slices][min(L,40)][M][d]
+ * and 1 KB of counters).  On the streamed path with
  * adapters the gate/up launch also computes LoRA-A and hands t over as
  * tagged words: the control block's word 0 counts the calls and word 160
  * holds sticky error bits (1 = a wait for t gave up), so the workspace must
@@ -308,8 +311,10 @@ qmlp_status qmlp_forward_layers(const qmlp_mlp *layers, int L, const void *x, in
                                 qmlp_stream stream);
 
 /* Which path qmlp_forward_layers takes for these blocks: 1 = streamed, 2 =
- * the batched stand-alone kernels, 3 = qmlp_forward per block (bfloat16),
- * 4 = matrix cores; 0 if the call would be rejected.  Host-only (it queries
+ * batched (each half on the matrix cores or the stand-alone kernels), 3 =
+ * qmlp_forward per block (bfloat16), 4 = matrix cores (3 <= M <= 16 in the
+ * W4/W2-GateUp form, d % 512 == 0, f % 256 == 0); 0 if the call would be
+ * rejected.  Host-only (it queries
  * the current device's compute-unit count). */
 int qmlp_layers_path(const qmlp_mlp *layers, int L, int M, qmlp_dtype dtype);
 
@@ -348,8 +353,9 @@ qmlp_status qmlp_forward_batch(const qmlp_mlp *layers, int L, const void *x, int
  * a decoder layer (q, k and v as one [q+2kv][d] matrix, o) and the LM head.
  * w[0..L-1] are host descriptors of one shape [n][k] and width (4, or 2 with
  * group 64/128), 1 <= L <= 40; x [L][M][k] and y [L][M][n] binary16,
- * 1 <= M <= 16 (M == 0 is a no-op).  One launch of the stand-alone down
- * kernel over the batch; no workspace.  n % 64 == 0, k % 64 == 0.
+ * 1 <= M <= 16 (M == 0 is a no-op).  One launch over the batch (from two
+ * tokens on the matrix cores where a row fits one workgroup, else the
+ * stand-alone down kernel); no workspace.  n % 64 == 0, k % 64 == 0.
  */
 qmlp_status qmlp_linear_batch(const qmlp_qweight *w, int L, const void *x, int M,
                               qmlp_dtype dtype, void *y, qmlp_stream stream);
@@ -366,7 +372,11 @@ qmlp_status qmlp_linear_batch(const qmlp_qweight *w, int L, const void *x, int M
  * arrays (routing runs on the GPU); ids outside [0, E) are a precondition
  * violation (the kernels clamp them, so nothing is read outside the
  * table).  1 <= k <= E, M <= 16, M*k <= 40.  Every (token, slot) pair runs
- * as one instance: an expert chosen by two tokens is read twice.  Two
+ * as one instance.  Where tokens share enough experts that reading each
+ * expert in use once saves more than its launches cost, the layer runs on the
+ * matrix cores: LoRA-A, gate/up and down over the experts in use, their
+ * instances side by side, and a combine launch over the instances' fp32
+ * outputs.  Otherwise an expert chosen by two tokens is read twice, in two
  * launches over the M*k instances: gate/up, whose first workgroups of each
  * instance compute LoRA-A (with adapters) and hand t to the others as tagged
  * words, then down.  With
@@ -379,7 +389,7 @@ qmlp_status qmlp_linear_batch(const qmlp_qweight *w, int L, const void *x, int M
  * block (uint32 words on 128-byte lines: word 0 counts the calls and tags
  * each call's t words, word 160 holds sticky error bits, 1 = a wait for t
  * gave up), t as tagged 64-bit words [M*k][2r], h and the per-instance
- * outputs.  The workspace must be ZERO before its first call, and zeroed
+ * outputs (fp32 on the matrix cores).  The workspace must be ZERO before its first call, and zeroed
  * again after a call failed or an error bit appeared (the results of that
  * call are invalid).  One workspace serves one call at a time: calls that
  * overlap in time on the same workspace race.

@@ -151,9 +151,10 @@ def summarize(kt_dir, pf_dir, pw_dir, kernel, copy_mib, out_md, commands, stream
     krows = []
     for part in parts:
         rows = [r for r in stats if part in r["Name"]]
-        if len(rows) != 1:
-            raise ValueError("kernel %r matches %d rows of the stats" % (part, len(rows)))
-        krows.append(dict(rows[0]))
+        if not rows:
+            raise ValueError("kernel %r matches no row of the stats" % part)
+        # several instantiations (other calls of the run): the step's is the longest in sum
+        krows.append(dict(max(rows, key=lambda r: float(r["Calls"]) * float(r["AverageNs"]))))
     # with the per-dispatch trace, the step's own dispatches give the figures
     traces = glob.glob(os.path.join(kt_dir, "*kernel_trace.csv"))
     if len(traces) == 1:
@@ -162,9 +163,11 @@ def summarize(kt_dir, pf_dir, pw_dir, kernel, copy_mib, out_md, commands, stream
         if ids is not None:
             dur = {int(r["Dispatch_Id"]): int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
                    for r in trows}
+            name = {int(r["Dispatch_Id"]): r["Kernel_Name"] for r in trows}
             for kr, idl in zip(krows, ids):
                 ns = [dur[i] for i in idl]
-                kr.update(Calls=len(ns), AverageNs=statistics.mean(ns), MinNs=min(ns), MaxNs=max(ns))
+                kr.update(Name=name[idl[0]], Calls=len(ns), AverageNs=statistics.mean(ns), MinNs=min(ns),
+                          MaxNs=max(ns))
     avg_us = sum(float(r["AverageNs"]) for r in krows) / 1e3
     copy_kib = copy_mib * 1024.0
     stream_kib = stream_mib * 1024.0
