@@ -24,13 +24,19 @@
 // and the last of them to finish (a counter per range) adds the slices in
 // order.  No workgroup waits for another.
 //
-// The arithmetic is that of decode_mfma.hip: codes enter as 1024 + q 2^j
-// (one and-or per pair; j >= 4, so that the offset's share of the fp32 sums
-// and their rounding stays small: at j from 0 the error against 64 bits was
-// 2 % larger), the activation is pre-scaled by 2^-j, a group's
-// accumulator starts at -(C + z X) with C = 1024 sum x' and X = sum 2^j x'
-// (formed on the matrix cores as products with constants, which leaves them
-// in the accumulator's own layout), and the group adds scale * acc in fp32.
+// The arithmetic: codes enter as 1024 + q 2^j (one and-or per pair; j >= 4,
+// so that the offset's share of the fp32 sums and their rounding stays small:
+// at j from 0 the error against 64 bits was 2 % larger) and the activation as
+// x' = x 2^(4 - j), so a code's product is 1024 x' + 16 q x and a tile's
+// finished sum is multiplied by 2^-4 once.  (With x 2^-j the factor is not
+// needed, but x' is binary16 and small activations lose more bits below its
+// normal range: a 4-bit linear on inputs of rms 6e-4 was 1.3e-3 off 64 bits
+// instead of 2.1e-4, and a 2-bit one 3.9e-3 instead of 3.2e-4, in a CPU model
+// of the operands.)  The products'
+// offset and the zero point come off as an fp32 contraction over the groups
+// of s and s z with C = 1024 sum x' and X = 16 sum x (formed on the matrix
+// cores as products with constants, which leaves them in the operand's own
+// layout), and a group adds scale * (its product) in fp32.
 // LoRA-B stays fp32: t is the A operand and B (exact in fp32) the B operand
 // of v_mfma_f32_16x16x4_f32, four ranks per instruction.
 //
@@ -165,7 +171,10 @@ __device__ __forceinline__ uint32_t pk_mul(uint32_t a, uint32_t b) {
 __device__ __forceinline__ constexpr uint32_t pow2_pair(int e) {      // binary16 2^e in both halves
     return (uint32_t)((15 + e) << 10) * 0x00010001u;
 }
-// Fraction position of pair p (0..3) of the matrix operand of half h.
+// Fraction position j of pair p (0..3) of the matrix operand of half h, and
+// the smallest of them: x' = x 2^(kPosMin - j).
+constexpr int kPosMin = 4;
+constexpr float kTileUnscale = 1.0f / 16.0f;               // 2^-kPosMin, of a finished sum
 template <int B, bool HALF>
 __device__ __forceinline__ constexpr int pair_pos(int h, int p) {
     if (B == 4) return p < 2 ? 4 : 6;
@@ -174,8 +183,10 @@ __device__ __forceinline__ constexpr int pair_pos(int h, int p) {
 }
 template <int B, bool HALF>
 __device__ __forceinline__ uint4 scale_pairs(uint4 v, int h) {
-    return make_uint4(pk_mul(v.x, pow2_pair(-pair_pos<B, HALF>(h, 0))), pk_mul(v.y, pow2_pair(-pair_pos<B, HALF>(h, 1))),
-                      pk_mul(v.z, pow2_pair(-pair_pos<B, HALF>(h, 2))), pk_mul(v.w, pow2_pair(-pair_pos<B, HALF>(h, 3))));
+    return make_uint4(pk_mul(v.x, pow2_pair(kPosMin - pair_pos<B, HALF>(h, 0))),
+                      pk_mul(v.y, pow2_pair(kPosMin - pair_pos<B, HALF>(h, 1))),
+                      pk_mul(v.z, pow2_pair(kPosMin - pair_pos<B, HALF>(h, 2))),
+                      pk_mul(v.w, pow2_pair(kPosMin - pair_pos<B, HALF>(h, 3))));
 }
 template <int B, bool HALF>
 __device__ __forceinline__ uint4 unscale_pairs(int h) {
@@ -205,7 +216,7 @@ __device__ __forceinline__ void act_convert(AOps<B, G>& a) {
     }
 }
 // The A operands of a step's offset and zero-point terms.  With C = sum x'
-// and X = sum 2^j x' of a token and group, the group's codes add
+// and X = sum 2^j x' (16 sum x) of a token and group, the group's codes add
 // s (p - 1024 C - z X), p their plain product with x'.  The second and third
 // terms of all groups are one fp32 contraction over groups, rows (s, s z)
 // against tokens (-1024 C, -X): v_mfma_f32_16x16x4_f32, where instruction m
@@ -621,6 +632,8 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, Tile
 #pragma unroll
                     for (int m = 0; m < NM; ++m) acc[m] += rd[(w * NM + m) * 64];
                 }
+#pragma unroll
+                for (int m = 0; m < NM; ++m) acc[m] *= kTileUnscale;
                 if constexpr (GU) {
                     if (r > 0) {
 #pragma unroll

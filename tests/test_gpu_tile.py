@@ -188,3 +188,54 @@ def test_shared_experts_match_oracle(q, d, f, gb, g, db, r, E, k, M, same):
     assert orc.max_rel_err(values_of(ys[0]), want) <= 1e-2
     assert torch.equal(ys[0], ys[1])
     assert q.workspace_errors(ws) == 0 and int(ws[0:4].view(torch.int32).item()) == 2
+
+
+# Small activations: the tile kernels scale an activation by up to 2^-s before
+# it is rounded to binary16 (s = 2 for 4-bit codes, 4 for 2-bit ones), so below
+# binary16's normal range it is off by at most 2^(s - 25), 2^(s - 25) /
+# sqrt(3) in the mean; the weights, the sums and the zero-point term add
+# nothing that counts, and the output is rounded to binary16 once (2^-11 /
+# sqrt(3) in the mean).  At rms 2^-11 that is 1.4e-4 and 5.6e-4 of the
+# activations (scaled by 2^-6 and 2^-8 they would be off by four and sixteen times as much).
+SMALL = 2.0 ** -11
+
+
+def _small_bar(bits, factor=1.0):
+    return float(np.hypot(2.0 ** -11, factor * 2.0 ** ((2 if bits == 4 else 4) - 25) / SMALL) / np.sqrt(3.0))
+
+
+@pytest.mark.parametrize("bits,g", [(4, 128), (4, 64), (4, 32), (2, 128), (2, 64)])
+@pytest.mark.parametrize("packed,M", [(False, 2), (False, 9), (True, 8)])
+def test_linear_small_activations(q, bits, g, packed, M):
+    """One step per operand and two (rows past twelve waves' steps at up to
+    eight tokens: two steps share an operand; 4-bit groups of 32 hold half
+    as long a row, and longer ones run the stand-alone kernel)."""
+    n, k = 256, (2560 if not packed else 5120 if (bits, g) == (4, 32) else 9216)
+    print("tile small linear", n, k, bits, g, "M", M, flush=True)
+    rng = np.random.default_rng([k, bits, g])
+    W = (4.0 * rng.standard_normal((n, k))).astype(np.float32)      # outputs well inside binary16
+    x = (SMALL * rng.standard_normal((1, M, k))).astype(np.float16)
+    y = values_of(q.linear_batch([_pack(q, W, bits, g)], torch.from_numpy(x).cuda())[0])
+    want = orc.down(orc.quantize(W, bits, g), x[0].astype(np.float64))
+    assert np.linalg.norm(y - want) / np.linalg.norm(want) <= _small_bar(bits)
+
+
+@pytest.mark.parametrize("bits,g", [(2, 128), (2, 64), (2, 32), (4, 128), (4, 64), (4, 32)])
+@pytest.mark.parametrize("M", [5, 16])
+def test_gateup_small_activations(q, bits, g, M):
+    """G and U of rms about 1/2, so h is about G U / 2 and takes each sum's
+    error once (in the mean sqrt(2) of it; 2 in the bar); the down weights pass h on as it is."""
+    d, f = 2560, 512
+    print("tile small gateup", bits, g, "M", M, flush=True)
+    rng = np.random.default_rng([M, bits, g])
+    Wg, Wu = ((20.0 * rng.standard_normal((f, d))).astype(np.float32) for _ in range(2))
+    Wd = np.zeros((d, f), np.float32)                               # y[:f] = h: scale 1/15, code 15
+    Wd[np.arange(f), np.arange(f)] = 1.0
+    x = (SMALL * rng.standard_normal((M, d))).astype(np.float16)
+    m = q.MLP(_pack(q, Wg, bits, g), _pack(q, Wu, bits, g), _pack(q, Wd, 4, 128), None, None, None, None)
+    y = values_of(q.forward(m, torch.from_numpy(x).cuda()))
+    want = orc.forward(orc.quantize(Wg, bits, g), orc.quantize(Wu, bits, g), orc.quantize(Wd, 4, 128),
+                       None, None, None, None, x.view(np.uint16))
+    # h is rounded to binary16 and its diagonal weight 15 s to the scale's: the oracle holds the same weight
+    bar = float(np.hypot(2.0 ** -11 / np.sqrt(3.0), _small_bar(bits, 2.0)))
+    assert np.linalg.norm(y - want) / np.linalg.norm(want) <= bar
