@@ -1,6 +1,7 @@
 // C ABI of libqmlp: argument validation, workspace layout and kernel dispatch.
 // Every check runs before the first launch, so a rejected call enqueues
 // nothing and writes nothing.
+#include <atomic>
 #include <cstring>
 #include <stddef.h>
 #include <stdint.h>
@@ -551,6 +552,20 @@ qmlp_status run_layers_batched(const qmlp_mlp* layers, int L, const char* xb, in
 }  // namespace
 
 namespace qmlp {
+
+int device_cus() {
+    static std::atomic<int> cache[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return 0;
+    int n = cache[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            return 0;
+        cache[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
 
 // Everything qmlp_forward checks before it looks at the workspace.
 qmlp_status forward_check(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype dtype, const void* y) {

@@ -626,20 +626,6 @@ __global__ void __launch_bounds__(NW * 64) mf_dn_kernel(BatchArgs b, int nb, int
     }
 }
 
-int mf_cu_count() {
-    static int cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
-        return 0;
-    if (cache[dev] == 0) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            return 0;
-        cache[dev] = n;
-    }
-    return cache[dev];
-}
-
 constexpr size_t kMfLds = 160 * 1024;
 
 int mf_mt(int M) { return M <= 4 ? 4 : M <= 8 ? 8 : 16; }
@@ -669,7 +655,7 @@ int mf_dn_chunk(int f, int g, int MT) {
     return ck < fr ? ck : fr;
 }
 int mf_grid(long items) {
-    const long c = mf_cu_count();
+    const long c = device_cus();
     return (int)(items < c ? items : c);
 }
 
@@ -682,7 +668,7 @@ bool mfma_supported(int M, int d, int f, int gg, int bg, int gd, int bd, int r, 
         return false;
     if (nb < 1 || nb > kBatchMax || d % 512 != 0 || f % 256 != 0)
         return false;
-    if (mf_cu_count() <= 0)
+    if (device_cus() <= 0)
         return false;
     const int MT = mf_mt(M);
     return mf_gu_lds(d, gg, MT) <= kMfLds && mf_dn_lds(mf_dn_chunk(f, gd, MT), gd, MT) <= kMfLds;

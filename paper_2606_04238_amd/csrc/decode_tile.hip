@@ -49,8 +49,11 @@
 #include "decode_common.h"
 #include "decode_launch.h"
 #include "mfma_tile.h"
+#include "tile_plan.h"
 
 namespace qmlp {
+
+static_assert(kTileBatch == kBatchMax, "one batch size");
 
 namespace {
 
@@ -413,24 +416,6 @@ __device__ __forceinline__ int route_row(unsigned long long mask, int j) {
     return row;
 }
 
-constexpr int kTileCounters = 256;                // words at the start of the scratch
-
-struct TilePlan {
-    int kw, tw;              // waves along K, tiles side by side
-    int mw;                  // gate/up: 2 where gate and up have waves of their own, else 1
-    int tg;                  // tiles of a tile lane per barrier
-    int sk, ns;              // K slices, steps of a row
-    int wgs;                 // workgroups per K slice
-    int wpb;                 // workgroups per block, 0: every workgroup its share of the whole batch
-    int tq, tr;              // tiles (of a block, of the batch) over those workgroups: quotient, remainder
-    int sq, sr;              // steps of a row over slices
-    int ipw, ikw;            // 2^16 / waves of a tile lane and / kw, rounded up (waves are below 16)
-    int pack;                // packed steps
-    int ts;                  // gate/up: slices of d in t; linear: floats of t to clear
-    int threads;
-    size_t lds;
-};
-
 // GU: gate and up of the batch's blocks -> h (MS = 2: a wave takes a tile's
 // gate, then its up; MS = 1: one of them, p.mw = 2).  Otherwise the down
 // weights of the descriptors on b.h -> b.y (binary16), with p.sk > 1 through
@@ -448,8 +433,8 @@ struct TilePlan {
 // the linear leaves fp32 [sk][nb][N] in scratch for the combine.
 // NSET register sets: NSET - 1 units
 // (the SPW steps of one matrix of one tile) are in flight per wave.
-template <int B, int G, bool GU, int MS, int SPW, bool PACK, bool RT, int NW, int NSET>
-__global__ void __launch_bounds__(NW * 64) tile_kernel(BatchArgs b, int nb, TilePlan p, float* scratch) {
+template <int B, int G, bool GU, int MS, int SPW, bool PACK, bool RT, int NSET>
+__global__ void __launch_bounds__(kTileWaves * 64) tile_kernel(BatchArgs b, int nb, TilePlan p, float* scratch) {
     typedef Lay<B, G> Y;
     static_assert(NSET % MS == 0, "a set holds one matrix or parity");
     static_assert(!PACK || (!GU && MS == 2), "packed steps: linear only");
@@ -808,146 +793,16 @@ __global__ void __launch_bounds__(256) tile_lora_kernel(BatchArgs b, int nb, int
     }
 }
 
-constexpr int kTileWaves = 12;                 // waves of a workgroup, 168 registers each
-constexpr size_t kTileLds = 159 * 1024;          // beside the routed batch's row table
-
-int tile_cu_count() {
-    static int cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
-        return 0;
-    if (cache[dev] == 0) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            return 0;
-        cache[dev] = n;
-    }
-    return cache[dev];
-}
-
-// Tiles side by side: as many as the workgroup's waves allow, but no more than
-// leave every compute unit a workgroup.
-int tile_tw(long tiles, int pw, int sk, int cus) {
-    const long most = kTileWaves / pw, spread = tiles * sk / cus;
-    return (int)(spread < 1 ? 1 : spread < most ? spread : most);
-}
-
-// Workgroups of a launch: one per compute unit over all slices, no more than
-// there are groups of TW tiles.
-int tile_wgs(long tiles, int tw, int sk, int cus) {
-    const long most = (tiles + tw - 1) / tw, per = cus / sk > 0 ? cus / sk : 1;
-    return (int)(most < per ? most : per);
-}
-
-// The kernel's divisions, done here.
-void tile_shares(TilePlan& p, long tiles) {
-    p.tq = (int)(tiles / p.wgs);
-    p.tr = (int)(tiles % p.wgs);
-    p.sq = p.ns / p.sk;
-    p.sr = p.ns % p.sk;
-    p.ipw = 65536 / (p.kw * p.mw) + 1;
-    p.ikw = 65536 / p.kw + 1;
-}
-
-// Tiles per barrier: up to four (a wave of its own adds each), as LDS allows;
-// false where not even one fits.
-bool tile_group(TilePlan& p, int nm, size_t more) {
-    p.tg = p.kw * p.mw < 4 ? p.kw * p.mw : 4;
-    for (;; --p.tg) {
-        p.lds = (size_t)2 * p.tg * p.tw * p.kw * nm * 1024 + more;
-        if (p.lds <= kTileLds)
-            return true;
-        if (p.tg == 1)
-            return false;
-    }
-}
-
-// Workgroups of their own for each block of a batch, or an even share of the
-// whole batch for every workgroup?  A workgroup that crosses into another block
-// stages new activations with no weights in flight, which measured 7 us, about
-// the time of kCross tiles; whole workgroups per block leave some compute units
-// without work or the largest share a tile longer.  Own workgroups against an
-// even share: 12 blocks of d = 2048, f = 6144 at M = 16 63 against 71 us, 20 of
-// d = f = 2880 69 against 74, 36 Qwen3-4B-shaped ones 227 against 230.
-void tile_blocks(TilePlan& p, int nb, int tpb, int cus) {
-    constexpr long kCross = 5;
-    p.wpb = 0;
-    const int per = cus / p.sk / nb < (tpb + p.tw - 1) / p.tw ? cus / p.sk / nb : (tpb + p.tw - 1) / p.tw;
-    if (nb == 1 || per < 1)
-        return;
-    const long all = (long)nb * tpb, shared = (all + p.wgs - 1) / p.wgs + kCross * p.tw;
-    if ((tpb + per - 1) / per <= shared) {
-        p.wpb = per;
-        p.wgs = per * nb;
-        p.tq = tpb / per;
-        p.tr = tpb % per;
-    }
-}
-
-// Gate/up: K = d.  Gate and up take waves of their own while both fit in one
-// workgroup (twice the waves share the stream of a short row), else every
-// wave takes a tile's gate, then its up.  Rows past kTileWaves steps do not
-// fit: false.
-bool plan_gateup(int M, int d, int f, int g, int bits, int r, int nb, TilePlan& p) {
-    const int cus = tile_cu_count();
-    if (cus <= 0 || M < 1 || M > 16 || nb < 1 || nb > kBatchMax || d % 64 != 0 || f % 16 != 0 || d % g != 0 ||
-        (bits != 2 && bits != 4) || (r != 0 && r != 8 && r != 16 && r != 32) ||
-        (long)f * d * bits / 8 >= (1l << 31) || (long)f * (d / g) * 4 >= (1l << 31))
-        return false;
-    const int cps = 1024 / bits;
-    p.ns = (d + cps - 1) / cps;
-    p.sk = 1;
-    p.pack = 0;
-    p.kw = p.ns;
-    p.mw = 2 * p.kw <= kTileWaves ? 2 : 1;
-    if (p.kw > kTileWaves)
-        return false;
-    p.tw = tile_tw((long)nb * (f / 16), p.kw * p.mw, 1, cus);
-    p.threads = p.tw * p.kw * p.mw * 64;
-    p.wgs = tile_wgs((long)nb * (f / 16), p.tw, 1, cus);
-    tile_shares(p, (long)nb * (f / 16));
-    tile_blocks(p, nb, f / 16, cus);
-    return tile_group(p, 2, r > 0 ? 8192 : 0);
-}
-
-// 4-bit groups of 32 hold one step per wave (two spill).
-int linear_spw(int g, int bits) { return bits == 4 && g != 32 ? 2 : 1; }
-
-// Any linear [n][k]: as few slices of k as fit the workgroup's registers, with
-// packed steps where that saves slices.
-bool plan_linear(int M, int n, int k, int g, int bits, int nb, TilePlan& p) {
-    const int cus = tile_cu_count();
-    if (cus <= 0 || M < 1 || M > 16 || nb < 1 || nb > kBatchMax || k % 64 != 0 || n % 16 != 0 || k % g != 0 ||
-        (bits != 2 && bits != 4) || (bits == 2 && g == 32) || (long)n * k * bits / 8 >= (1l << 31) ||
-        (long)n * (k / g) * 4 >= (1l << 31))
-        return false;
-    const int cps = 1024 / bits, spw = linear_spw(g, bits);
-    p.ns = (k + cps - 1) / cps;
-    p.pack = M <= 8 && p.ns > kTileWaves * spw ? 1 : 0;
-    const int per = spw << p.pack;                         // steps per wave
-    p.sk = (p.ns + kTileWaves * per - 1) / (kTileWaves * per);
-    if ((long)p.sk * nb * M * n * 4 >= (1l << 31) || p.sk > cus)
-        return false;
-    p.kw = ((p.ns + p.sk - 1) / p.sk + per - 1) / per;
-    p.mw = 1;
-    p.tw = tile_tw((long)nb * (n / 16), p.kw, p.sk, cus);
-    p.threads = p.tw * p.kw * 64;
-    p.wgs = tile_wgs((long)nb * (n / 16), p.tw, p.sk, cus);
-    tile_shares(p, (long)nb * (n / 16));
-    tile_blocks(p, nb, n / 16, cus);
-    return tile_group(p, 1, 0);
-}
-
 }  // namespace
 
 bool tile_gateup_supported(int M, int d, int f, int g, int bits, int r, int nb) {
     TilePlan p;
-    return plan_gateup(M, d, f, g, bits, r, nb, p);
+    return plan_gateup(M, d, f, g, bits, r, nb, device_cus(), p);
 }
 
 int tile_linear_slices(int M, int n, int k, int g, int bits, int nb) {
     TilePlan p;
-    return plan_linear(M, n, k, g, bits, nb, p) && (p.sk == 1 || p.wgs <= kTileCounters) ? p.sk : 0;
+    return plan_linear(M, n, k, g, bits, nb, device_cus(), p) && (p.sk == 1 || p.wgs <= kTileCounters) ? p.sk : 0;
 }
 size_t tile_scratch_bytes(int sk, int nb, int M, int n) {
     return sk > 1 ? (size_t)kTileCounters * 4 + (size_t)sk * nb * M * n * 4 : 0;
@@ -975,13 +830,13 @@ hipError_t launch_lora_a_tile(const BatchArgs& b, int nb, int slices, hipStream_
 
 hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scratch, hipStream_t st) {
     TilePlan p;
-    if (!plan_gateup(b.M, b.d, b.f, b.gg, b.bg, b.r, nb, p))
+    if (!plan_gateup(b.M, b.d, b.f, b.gg, b.bg, b.r, nb, device_cus(), p))
         return hipErrorInvalidValue;
     p.ts = slices;
 #define QMLP_TGU_R(B_, G_, R_)                                                            \
     if (b.bg == B_ && b.gg == G_ && (b.route != nullptr) == R_)                           \
-        return p.mw == 2 ? tile_run(tile_kernel<B_, G_, true, 1, 1, false, R_, kTileWaves, 4>, b, nb, p, scratch, st) \
-                         : tile_run(tile_kernel<B_, G_, true, 2, 1, false, R_, kTileWaves, 4>, b, nb, p, scratch, st);
+        return p.mw == 2 ? tile_run(tile_kernel<B_, G_, true, 1, 1, false, R_, 4>, b, nb, p, scratch, st) \
+                         : tile_run(tile_kernel<B_, G_, true, 2, 1, false, R_, 4>, b, nb, p, scratch, st);
 #define QMLP_TGU(B_, G_) QMLP_TGU_R(B_, G_, false) QMLP_TGU_R(B_, G_, true)
     QMLP_TGU(2, 128) QMLP_TGU(2, 64) QMLP_TGU(2, 32) QMLP_TGU(4, 128) QMLP_TGU(4, 64) QMLP_TGU(4, 32)
     return hipErrorInvalidValue;
@@ -990,14 +845,14 @@ hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scr
 hipError_t launch_linear_tile(const BatchArgs& b, int nb, int clear_t, float* scratch, hipStream_t st) {
     TilePlan p;
     // a routed batch: up to 16 operand rows, partials always
-    if (!plan_linear(b.route ? 16 : b.M, b.d, b.f, b.gd, b.bd, nb, p) || ((p.sk > 1 || b.route) && !scratch))
+    if (!plan_linear(b.route ? 16 : b.M, b.d, b.f, b.gd, b.bd, nb, device_cus(), p) || ((p.sk > 1 || b.route) && !scratch))
         return hipErrorInvalidValue;
     p.ts = clear_t;
 #define QMLP_TLN(B_, G_, S_)                                                              \
     if (b.bd == B_ && b.gd == G_)                                                         \
-        return b.route ? tile_run(tile_kernel<B_, G_, false, 1, S_, false, true, kTileWaves, 3>, b, nb, p, scratch, st) \
-               : p.pack ? tile_run(tile_kernel<B_, G_, false, 2, S_, true, false, kTileWaves, 2>, b, nb, p, scratch, st) \
-                        : tile_run(tile_kernel<B_, G_, false, 1, S_, false, false, kTileWaves, 3>, b, nb, p, scratch, st);
+        return b.route ? tile_run(tile_kernel<B_, G_, false, 1, S_, false, true, 3>, b, nb, p, scratch, st) \
+               : p.pack ? tile_run(tile_kernel<B_, G_, false, 2, S_, true, false, 2>, b, nb, p, scratch, st) \
+                        : tile_run(tile_kernel<B_, G_, false, 1, S_, false, false, 3>, b, nb, p, scratch, st);
     QMLP_TLN(4, 128, 2) QMLP_TLN(4, 64, 2) QMLP_TLN(4, 32, 1) QMLP_TLN(2, 128, 1) QMLP_TLN(2, 64, 1)
     return hipErrorInvalidValue;
 }

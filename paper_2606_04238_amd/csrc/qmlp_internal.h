@@ -13,6 +13,9 @@ namespace qmlp {
 // (descriptor, M, dtype, x and y); QMLP_OK for M == 0.
 qmlp_status forward_check(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype dtype, const void* y);
 
+// Compute units of the current device (asked once per device), 0 without one.
+int device_cus();
+
 // Codes per unit of a row's code stream: 32 at 4 bits and 64 at 2 bits (one
 // 16-byte load); at 3 bits 64 (16 bytes of the 2-bit plane and 8 bytes of
 // the 1-bit plane).
