@@ -459,21 +459,11 @@ __global__ void __launch_bounds__(kTileWaves * 64) tile_kernel(BatchArgs b, int 
     const int rb = K * B / 8, ng = K / G;
     const int tpb = N / 16;
     const int id = RT ? route_id(b, nb, lane) : 0;
-    const int total = RT ? route_blocks(b, id) * tpb : 0;
-    // This workgroup's tiles [t0, t1): of a block's, over p.wpb workgroups of its own, or an even share of
-    // the whole batch's.
-    int l, t0, t1;
-    if (!RT && p.wpb > 0) {
-        l = (unsigned)wg / (unsigned)p.wpb;
-        const int i = wg - l * p.wpb;
-        t0 = l * tpb + i * p.tq + min(i, p.tr);
-        t1 = t0 + p.tq + (i < p.tr ? 1 : 0);
-    } else {
-        const int tq = RT ? (int)((unsigned)total / (unsigned)p.wgs) : p.tq, tr = RT ? total - tq * p.wgs : p.tr;
-        t0 = wg * tq + min(wg, tr);
-        t1 = t0 + tq + (wg < tr ? 1 : 0);
-        l = nb == 1 ? 0 : (unsigned)t0 / (unsigned)tpb;
-    }
+    const TileRange own_tiles = RT            ? tile_routed_range(wg, p.wgs, route_blocks(b, id), tpb, TW)
+                                : p.wpb > 0 ? tile_range(wg, p.wpb, tpb, p.tq, p.tr, true)
+                                            : tile_range(wg, p.wgs, tpb, p.tq, p.tr, false);
+    const int t0 = own_tiles.t0, t1 = own_tiles.t1;
+    int l = own_tiles.l;
     __shared__ int rows[2][16];                            // RT: instances of a block's operand rows
     KBatchM* kb = kbm();
     uint32_t ol[SPW * SK2];                                // lane's offsets of the code loads
@@ -797,12 +787,12 @@ __global__ void __launch_bounds__(256) tile_lora_kernel(BatchArgs b, int nb, int
 
 bool tile_gateup_supported(int M, int d, int f, int g, int bits, int r, int nb) {
     TilePlan p;
-    return plan_gateup(M, d, f, g, bits, r, nb, device_cus(), p);
+    return plan_gateup(M, d, f, g, bits, r, nb, false, device_cus(), p);
 }
 
 int tile_linear_slices(int M, int n, int k, int g, int bits, int nb) {
     TilePlan p;
-    return plan_linear(M, n, k, g, bits, nb, device_cus(), p) && (p.sk == 1 || p.wgs <= kTileCounters) ? p.sk : 0;
+    return plan_linear(M, n, k, g, bits, nb, false, device_cus(), p) && (p.sk == 1 || p.wgs <= kTileCounters) ? p.sk : 0;
 }
 size_t tile_scratch_bytes(int sk, int nb, int M, int n) {
     return sk > 1 ? (size_t)kTileCounters * 4 + (size_t)sk * nb * M * n * 4 : 0;
@@ -830,7 +820,7 @@ hipError_t launch_lora_a_tile(const BatchArgs& b, int nb, int slices, hipStream_
 
 hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scratch, hipStream_t st) {
     TilePlan p;
-    if (!plan_gateup(b.M, b.d, b.f, b.gg, b.bg, b.r, nb, device_cus(), p))
+    if (!plan_gateup(b.M, b.d, b.f, b.gg, b.bg, b.r, nb, b.route != nullptr, device_cus(), p))
         return hipErrorInvalidValue;
     p.ts = slices;
 #define QMLP_TGU_R(B_, G_, R_)                                                            \
@@ -845,7 +835,7 @@ hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scr
 hipError_t launch_linear_tile(const BatchArgs& b, int nb, int clear_t, float* scratch, hipStream_t st) {
     TilePlan p;
     // a routed batch: up to 16 operand rows, partials always
-    if (!plan_linear(b.route ? 16 : b.M, b.d, b.f, b.gd, b.bd, nb, device_cus(), p) || ((p.sk > 1 || b.route) && !scratch))
+    if (!plan_linear(b.route ? 16 : b.M, b.d, b.f, b.gd, b.bd, nb, b.route != nullptr, device_cus(), p) || ((p.sk > 1 || b.route) && !scratch))
         return hipErrorInvalidValue;
     p.ts = clear_t;
 #define QMLP_TLN(B_, G_, S_)                                                              \

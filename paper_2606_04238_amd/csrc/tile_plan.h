@@ -73,26 +73,55 @@ inline bool tile_group(TilePlan& p, int nm, size_t more) {
 // without work or the largest share a tile longer.  Own workgroups against an
 // even share: 12 blocks of d = 2048, f = 6144 at M = 16 63 against 71 us, 20 of
 // d = f = 2880 69 against 74, 36 Qwen3-4B-shaped ones 227 against 230.
+// nb blocks of tpb tiles, tw side by side, over wgs workgroups: the workgroups
+// of each block, 0 for even shares.
+constexpr int tile_own(int wgs, int nb, int tpb, int tw) {
+    constexpr int kCross = 5;
+    const int per = wgs / nb < (tpb + tw - 1) / tw ? wgs / nb : (tpb + tw - 1) / tw;
+    const int shared = (int)(((long)nb * tpb + wgs - 1) / wgs) + kCross * tw;
+    return nb > 1 && per >= 1 && (tpb + per - 1) / per <= shared ? per : 0;
+}
 inline void tile_blocks(TilePlan& p, int nb, int tpb, int cus) {
-    constexpr long kCross = 5;
-    p.wpb = 0;
-    const int per = cus / p.sk / nb < (tpb + p.tw - 1) / p.tw ? cus / p.sk / nb : (tpb + p.tw - 1) / p.tw;
-    if (nb == 1 || per < 1)
-        return;
-    const long all = (long)nb * tpb, shared = (all + p.wgs - 1) / p.wgs + kCross * p.tw;
-    if ((tpb + per - 1) / per <= shared) {
-        p.wpb = per;
-        p.wgs = per * nb;
-        p.tq = tpb / per;
-        p.tr = tpb % per;
+    p.wpb = tile_own(cus / p.sk, nb, tpb, p.tw);
+    if (p.wpb > 0) {
+        p.wgs = p.wpb * nb;
+        p.tq = tpb / p.wpb;
+        p.tr = tpb % p.wpb;
     }
+}
+
+// The tiles [t0, t1) of workgroup wg, the first of them of block l.
+struct TileRange {
+    int l, t0, t1;
+};
+constexpr TileRange tile_range(int wg, int wgs, int tpb, int tq, int tr, bool own) {
+    // workgroups 0 .. tr - 1 (of a block's own ones, or of all) take a tile more
+    const int l = own ? (int)((unsigned)wg / (unsigned)wgs) : 0;
+    const int i = own ? wg - l * wgs : wg;
+    const int t0 = l * tpb + i * tq + (i < tr ? i : tr);
+    return {own ? l : (int)((unsigned)t0 / (unsigned)tpb), t0, t0 + tq + (i < tr ? 1 : 0)};
+}
+// ... of a routed batch, whose blocks are the nv experts that have instances:
+// known in the kernel only, so the launch has workgroups for every compute
+// unit and the kernel applies the rule above (workgroups past the experts'
+// own stay idle).  With the shares made on the host for the instances (40 of
+// them on 240 workgroups) 20B-class layers at 8, 9 and 10 tokens took 85-89,
+// 88-95 and 89-99 us over four routings, this way 78-83, 83-85 and 84-89; even
+// shares throughout 94 against 87 where the 240 happened to divide the experts.
+constexpr TileRange tile_routed_range(int wg, int wgs, int nv, int tpb, int tw) {
+    const int own = tile_own(wgs, nv, tpb, tw);
+    if (own > 0 && wg >= own * nv)
+        return {0, 0, 0};
+    const int over = own > 0 ? own : wgs, tiles = own > 0 ? tpb : nv * tpb;
+    const int tq = (int)((unsigned)tiles / (unsigned)over);
+    return tile_range(wg, over, tpb, tq, tiles - tq * over, own > 0);
 }
 
 // Gate/up: K = d.  Gate and up take waves of their own while both fit in one
 // workgroup (twice the waves share the stream of a short row), else every
 // wave takes a tile's gate, then its up.  Rows past kTileWaves steps do not
 // fit: false.
-inline bool plan_gateup(int M, int d, int f, int g, int bits, int r, int nb, int cus, TilePlan& p) {
+inline bool plan_gateup(int M, int d, int f, int g, int bits, int r, int nb, bool routed, int cus, TilePlan& p) {
     if (cus <= 0 || M < 1 || M > 16 || nb < 1 || nb > kTileBatch || d % 64 != 0 || f % 16 != 0 || d % g != 0 ||
         (bits != 2 && bits != 4) || (r != 0 && r != 8 && r != 16 && r != 32) ||
         (long)f * d * bits / 8 >= (1l << 31) || (long)f * (d / g) * 4 >= (1l << 31))
@@ -108,8 +137,10 @@ inline bool plan_gateup(int M, int d, int f, int g, int bits, int r, int nb, int
     p.tw = tile_tw((long)nb * (f / 16), p.kw * p.mw, 1, cus);
     p.threads = p.tw * p.kw * p.mw * 64;
     p.wgs = tile_wgs((long)nb * (f / 16), p.tw, 1, cus);
+    p.wpb = 0;
     tile_shares(p, (long)nb * (f / 16));
-    tile_blocks(p, nb, f / 16, cus);
+    if (!routed)
+        tile_blocks(p, nb, f / 16, cus);
     return tile_group(p, 2, r > 0 ? 8192 : 0);
 }
 
@@ -118,7 +149,7 @@ inline int linear_spw(int g, int bits) { return bits == 4 && g != 32 ? 2 : 1; }
 
 // Any linear [n][k]: as few slices of k as fit the workgroup's registers, with
 // packed steps where that saves slices.
-inline bool plan_linear(int M, int n, int k, int g, int bits, int nb, int cus, TilePlan& p) {
+inline bool plan_linear(int M, int n, int k, int g, int bits, int nb, bool routed, int cus, TilePlan& p) {
     if (cus <= 0 || M < 1 || M > 16 || nb < 1 || nb > kTileBatch || k % 64 != 0 || n % 16 != 0 || k % g != 0 ||
         (bits != 2 && bits != 4) || (bits == 2 && g == 32) || (long)n * k * bits / 8 >= (1l << 31) ||
         (long)n * (k / g) * 4 >= (1l << 31))
@@ -135,8 +166,10 @@ inline bool plan_linear(int M, int n, int k, int g, int bits, int nb, int cus, T
     p.tw = tile_tw((long)nb * (n / 16), p.kw, p.sk, cus);
     p.threads = p.tw * p.kw * 64;
     p.wgs = tile_wgs((long)nb * (n / 16), p.tw, p.sk, cus);
+    p.wpb = 0;
     tile_shares(p, (long)nb * (n / 16));
-    tile_blocks(p, nb, n / 16, cus);
+    if (!routed)
+        tile_blocks(p, nb, n / 16, cus);
     return tile_group(p, 1, 0);
 }
 
