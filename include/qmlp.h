@@ -128,9 +128,14 @@ size_t qmlp_meta_bytes(int n_out, int k_in, int group);
  * sticky error bits: 1 = t wait timed out, 2 = h wait timed out), then t
  * (fp32), h (activation type [M][f]), on the prefill path lora_scale * t in
  * bfloat16, and on the decode path the one-kernel layer's tagged hand-off
- * words (one [4][64] block of 64-bit words per compute unit, [4][f] 32-bit),
- * and on the prefill path, when the down projection splits f into slices
- * to fill the chip, the slices' fp32 partial sums [S][M][d].  The workspace must be ZERO before
+ * words (one [4][64] block of 64-bit words per compute unit, [4][f] 32-bit;
+ * where the block's launches on the matrix cores need more bytes than those,
+ * for LoRA-A's slices and the fp32 partial sums [slices][M][d] of long down
+ * rows, as many as they need), and on the prefill path, when the down projection splits f into slices
+ * to fill the chip, the slices' fp32 partial sums [S][M][d].  qmlp_forward
+ * also takes a decode workspace without the bytes for long down rows beyond
+ * the hand-off words; they then run the stand-alone kernel, which is slower.
+ * The workspace must be ZERO before
  * its first call, and zeroed again before it serves a block of another shape
  * or after an error bit appeared (the results of that call are invalid).
  * One workspace serves one call at a time: calls that overlap in time on the
@@ -201,9 +206,10 @@ qmlp_status qmlp_forward(const qmlp_mlp *mlp, const void *x, int M, qmlp_dtype d
  * of qmlp_noalloc_scratch_bytes() (1 MiB) in this library's device memory,
  * one per GPU, held until the process ends; the call allocates and frees
  * nothing.  Binary16 decode only (1 <= M <= 16): QMLP_ERR_UNSUPPORTED for
- * bfloat16, QMLP_ERR_WORKSPACE when qmlp_workspace_bytes(mlp, M, dtype)
- * exceeds the array (the Qwen3-4B, Qwen3-8B and 14B-class blocks fit up to
- * M = 16; d = 8192, f = 32768 fits up to M = 7).  Each call first clears the part of the array
+ * bfloat16, QMLP_ERR_WORKSPACE when the smallest workspace qmlp_forward
+ * takes exceeds the array (on 256 compute units the Qwen3-4B block fits up to
+ * M = 16, the Qwen3-8B one up to M = 13, the 14B-class one up to M = 7; d =
+ * 8192, f = 32768 does not).  Each call first clears the part of the array
  * the block uses (one small fill kernel, then the kernels of qmlp_forward,
  * on `stream`), so it never depends on an earlier call's contents.  All
  * calls on one GPU share its array: calls that overlap in time on the same

@@ -130,8 +130,8 @@ int tile_slices(const qmlp_qweight* w, int M, int nb) {
 // [T: M x 2r bfloat16, prefill only][t64: one [4][64] copy of tagged words
 // per block of the one-kernel layer, h32: 4 x f tagged words -- decode only,
 // that kernel's hand-offs; where the block runs on the tile kernels instead,
-// the same bytes hold LoRA-A's slices and the down slices' counters and
-// partial sums, zero again after the call].  t is M x 2r on the decode path
+// the same bytes, or as many more as these take, hold LoRA-A's slices and the
+// down slices' counters and partial sums, zero again after the call].  t is M x 2r on the decode path
 // and S x M x 2r split-K partials on the prefill path.
 constexpr size_t kCtlBytes = 1024;
 
@@ -159,13 +159,16 @@ size_t ws_t64_bytes() { return (size_t)fused_grid() * 256 * 8; }
 size_t ws_tag_bytes(const qmlp_mlp* mlp, qmlp_dtype dtype) {
     return dtype == QMLP_F16 ? ws_t64_bytes() + round256((size_t)4 * mlp->gate.n_out * 4) : 0;
 }
+// Bytes up to the hand-off words.
+size_t ws_head_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
+    return kCtlBytes + ws_t_bytes(mlp, M, dtype) + ws_h_bytes(mlp, M) + ws_T_bytes(mlp, M, dtype);
+}
 size_t ws_part_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
     return dtype == QMLP_BF16 ? round256(prefill_down_part_bytes(M, mlp->gate.k_in, mlp->gate.n_out)) : 0;
-}
-// Everything qmlp_forward carves from its workspace.
-size_t ws_total_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
-    return kCtlBytes + ws_t_bytes(mlp, M, dtype) + ws_h_bytes(mlp, M) + ws_T_bytes(mlp, M, dtype) +
-           ws_tag_bytes(mlp, dtype) + ws_part_bytes(mlp, M, dtype);
+}// The least a call takes: without room for more, down slices whose sums do not
+// fit the hand-off words' bytes run the stand-alone kernel.
+size_t ws_least_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
+    return ws_head_bytes(mlp, M, dtype) + ws_tag_bytes(mlp, dtype) + ws_part_bytes(mlp, M, dtype);
 }
 
 size_t tile_t_bytes(const qmlp_mlp* mlp, int M) {
@@ -181,16 +184,33 @@ int down_slices(const qmlp_mlp* mlp, int M, int nb, bool gateup) {
 bool block_tile_gateup(const qmlp_mlp* mlp, int M) {
     return !fused_mlp(mlp, M) && tile_gateup(mlp, M, 1);
 }
-// ... of a single block: the scratch sits in the hand-off area.
-int block_slices(const qmlp_mlp* mlp, int M) {
+// What a single block's launches on the tile kernels put where the hand-off
+// words are: LoRA-A's slices and the scratch of sk down slices.
+size_t block_tile_bytes(const qmlp_mlp* mlp, int M, int sk) {
+    return tile_t_bytes(mlp, M) + tile_scratch_bytes(sk, 1, M, mlp->gate.k_in);
+}
+// The down slices of a single block whose workspace has `room` bytes from the
+// hand-off words on (0: stand-alone).
+int block_slices(const qmlp_mlp* mlp, int M, size_t room) {
     const int sk = down_slices(mlp, M, 1, block_tile_gateup(mlp, M));
-    return tile_t_bytes(mlp, M) + tile_scratch_bytes(sk, 1, M, mlp->gate.k_in) <= ws_tag_bytes(mlp, QMLP_F16) ? sk : 0;
+    return block_tile_bytes(mlp, M, sk) <= room ? sk : 0;
+}
+size_t ws_tile_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
+    if (dtype != QMLP_F16 || fused_mlp(mlp, M))
+        return 0;
+    return round256(block_tile_bytes(mlp, M, block_slices(mlp, M, SIZE_MAX)));
+}
+// Everything qmlp_forward carves from its workspace.
+size_t ws_total_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
+    const size_t least = ws_least_bytes(mlp, M, dtype),
+                 tile = ws_head_bytes(mlp, M, dtype) + ws_tile_bytes(mlp, M, dtype);
+    return least > tile ? least : tile;
 }
 
 Workspace carve(const qmlp_mlp* mlp, int M, qmlp_dtype dtype, void* ws) {
     char* base = static_cast<char*>(ws);
     const size_t tb = ws_t_bytes(mlp, M, dtype), hb = ws_h_bytes(mlp, M);
-    char* tag = base + kCtlBytes + tb + hb + ws_T_bytes(mlp, M, dtype);
+    char* tag = base + ws_head_bytes(mlp, M, dtype);
     char* part = tag + ws_tag_bytes(mlp, dtype);
     return {reinterpret_cast<unsigned*>(base), reinterpret_cast<float*>(base + kCtlBytes),
             reinterpret_cast<uint16_t*>(base + kCtlBytes + tb),
@@ -299,20 +319,20 @@ BatchArgs block_batch(const qmlp_mlp* mlp, int M) {
     return b;
 }
 
-// The gate/up half: LoRA-A projection then the fused kernel.  With `down` the
-// block's down half follows on the tile kernels, whose launch clears the
-// LoRA-A slices; alone, LoRA-A takes the one slice of t.
-qmlp_status run_gateup(const qmlp_mlp* mlp, const void* x, int M, uint16_t* h, const Workspace& w, bool down,
+// The gate/up half: LoRA-A projection then the fused kernel.  With sk > 0 the
+// block's down half follows on the tile kernels in sk slices, whose launch
+// clears the LoRA-A slices; alone, LoRA-A takes the one slice of t.
+qmlp_status run_gateup(const qmlp_mlp* mlp, const void* x, int M, uint16_t* h, const Workspace& w, int sk,
                        hipStream_t st) {
     if (block_tile_gateup(mlp, M)) {
         BatchArgs b = block_batch(mlp, M);
         b.x = static_cast<const uint16_t*>(x);
         b.h = h;
-        b.t = down ? w.tile_t : w.t;
-        const int ts = down ? kLoraSlices : 1;
+        b.t = sk > 0 ? w.tile_t : w.t;
+        const int ts = sk > 0 ? kLoraSlices : 1;
         hipError_t e = mlp->rank > 0 ? launch_lora_a_tile(b, 1, ts, st) : hipSuccess;
         if (e == hipSuccess)
-            e = launch_gateup_tile(b, 1, ts, down && block_slices(mlp, M) > 1 ? w.tile_scratch : nullptr, st);
+            e = launch_gateup_tile(b, 1, ts, sk > 1 ? w.tile_scratch : nullptr, st);
         return from_hip(e);
     }
     if (mlp->rank > 0) {
@@ -581,6 +601,8 @@ qmlp_status forward_check(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype 
     return QMLP_OK;
 }
 
+size_t forward_least_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) { return ws_least_bytes(mlp, M, dtype); }
+
 }  // namespace qmlp
 
 extern "C" {
@@ -644,7 +666,7 @@ qmlp_status qmlp_gateup_w2_lora(const qmlp_mlp* mlp, const void* x, int M, qmlp_
     if (dtype == QMLP_BF16)
         return run_prefill_gateup(mlp, x, M, static_cast<uint16_t*>(h), w,
                                   static_cast<hipStream_t>(stream));
-    return run_gateup(mlp, x, M, static_cast<uint16_t*>(h), w, false, static_cast<hipStream_t>(stream));
+    return run_gateup(mlp, x, M, static_cast<uint16_t*>(h), w, 0, static_cast<hipStream_t>(stream));
 }
 
 qmlp_status qmlp_down_w4(const qmlp_qweight* down, const void* h, int M, qmlp_dtype dtype,
@@ -679,7 +701,7 @@ qmlp_status qmlp_forward(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype d
     qmlp_status s = qmlp::forward_check(mlp, x, M, dtype, y);
     if (s != QMLP_OK || M == 0)
         return s;
-    if (!ws || ws_bytes < qmlp_workspace_bytes(mlp, M, dtype))
+    if (!ws || ws_bytes < ws_least_bytes(mlp, M, dtype))
         return QMLP_ERR_WORKSPACE;
     if (!aligned16(ws))
         return QMLP_ERR_ALIGN;
@@ -697,8 +719,8 @@ qmlp_status qmlp_forward(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype d
                                      static_cast<const uint16_t*>(mlp->A_gate),
                                      static_cast<const uint16_t*>(mlp->A_up), w.t64, w.h32, w.ctl,
                                      st));
-    const int sk = block_slices(mlp, M);
-    s = run_gateup(mlp, x, M, w.h, w, sk > 0, st);
+    const int sk = block_slices(mlp, M, ws_bytes - ws_head_bytes(mlp, M, dtype));
+    s = run_gateup(mlp, x, M, w.h, w, sk, st);
     if (s != QMLP_OK)
         return s;
     return run_down(&mlp->down, w.h, M, y, sk, w.tile_scratch, w.tile_t,

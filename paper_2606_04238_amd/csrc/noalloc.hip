@@ -74,7 +74,9 @@ extern "C" qmlp_status qmlp_forward_noalloc(const qmlp_mlp* mlp, const void* x, 
         return s;
     if (dtype != QMLP_F16)
         return QMLP_ERR_UNSUPPORTED;
-    const size_t need = qmlp_workspace_bytes(mlp, M, dtype);
+    size_t need = qmlp_workspace_bytes(mlp, M, dtype);
+    if (need > kScratchBytes)
+        need = qmlp::forward_least_bytes(mlp, M, dtype);
     if (need == 0 || need > kScratchBytes)
         return QMLP_ERR_WORKSPACE;
     void* ws = nullptr;

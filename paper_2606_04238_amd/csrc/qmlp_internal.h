@@ -12,6 +12,8 @@ namespace qmlp {
 // The argument checks of qmlp_forward that precede its workspace checks
 // (descriptor, M, dtype, x and y); QMLP_OK for M == 0.
 qmlp_status forward_check(const qmlp_mlp* mlp, const void* x, int M, qmlp_dtype dtype, const void* y);
+// The smallest workspace qmlp_forward takes (qmlp_workspace_bytes may ask for more).
+size_t forward_least_bytes(const qmlp_mlp* mlp, int M, qmlp_dtype dtype);
 
 // Compute units of the current device (asked once per device), 0 without one.
 int device_cus();

@@ -159,6 +159,29 @@ def test_slices_leave_the_workspace_clean(q, M):
         assert orc.max_rel_err(values_of(y), want[:k]) <= 1e-2
 
 
+@pytest.mark.parametrize("M", [8, 13, 16])
+def test_partial_sums_get_their_workspace(q, M):
+    """Three slices of f (12 steps of 256 codes a slice) of a wide block: their
+    partials pass the hand-off words' bytes at 16 tokens, and the workspace
+    has room for them.  The smaller one of the no-allocation entry point
+    serves as well, on the stand-alone down kernel where they do not fit."""
+    d, f, r = 4096, 9216, 16
+    print("tile partials", M, flush=True)
+    cfg = wl.Config("tile_parts", M=M, d=d, f=f, g=64, r=r, L=1)
+    m, xb, ref = _block(q, cfg, 0, 2, 64, 4, 32)
+    r256 = lambda v: (v + 255) // 256 * 256
+    head = 1024 + r256(M * 2 * r * 4) + r256(M * f * 2)
+    assert q.workspace_bytes(m, M) >= head + r256(4 * M * 2 * r * 4) + 1024 + (2 if M <= 8 else 3) * M * d * 4
+    x = act_tensor(xb)
+    ws = q.workspace(m, M)
+    y = q.forward(m, x, ws=ws)
+    want = ref(xb)
+    torch.cuda.synchronize()
+    assert orc.max_rel_err(values_of(y), want) <= 1e-2
+    assert torch.equal(q.forward(m, x, ws=ws), y) and not bool(ws[head:].any())
+    assert orc.max_rel_err(values_of(q.forward_noalloc(m, x)), want) <= 1e-2
+
+
 @pytest.mark.parametrize("d,f,gb,g,db,r,E,k,M,same", [
     (2048, 1600, 2, 64, 4, 16, 4, 4, 10, False),       # every expert shared by all tokens
     (1600, 2048, 2, 64, 4, 32, 5, 4, 10, True),        # all forty instances on one expert: three operands of rows
