@@ -437,9 +437,9 @@ qmlp_status qmlp_dequant(const qmlp_qweight *w, uint16_t *w_f16, qmlp_stream str
  * 1 when the whole layer runs as one fused kernel (the decode shapes it
  * covers), 2 or 3 when it runs as the LoRA-A, gate/up and down kernels in
  * stream order; a bfloat16 prefill chunk makes LoRA-A and its reduction
- * (with an adapter), gate/up, down, and, when down splits f into slices to
- * fill the chip (f a multiple of 128 and fewer than 512 token x row tiles),
- * the slices' reduction; 0 if the call would be rejected.  Host-only,
+ * (with an adapter), gate/up, down, and, when down splits f into slices (f a
+ * multiple of 128, and the slices' workgroups stay within about one round
+ * over the compute units), the slices' reduction; 0 if the call would be rejected.  Host-only,
  * enqueues nothing. */
 int qmlp_forward_launches(const qmlp_mlp *mlp, int M, qmlp_dtype dtype);
 

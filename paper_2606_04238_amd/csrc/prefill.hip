@@ -28,6 +28,7 @@
 #include "qmlp_device.h"
 #include "qmlp_internal.h"
 #include "decode_launch.h"
+#include "prefill_plan.h"
 
 namespace qmlp {
 namespace {
@@ -38,7 +39,6 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int PF_BM = 128;     // tokens per block tile
-constexpr int PF_BK = 64;      // input elements per step
 constexpr int PF_NT = 256;     // threads per block
 
 __device__ __forceinline__ int swz(int r, int c) { return r * 8 + (c ^ ((r >> 1) & 7)); }
@@ -379,7 +379,6 @@ __global__ void __launch_bounds__(NT) pf_down_kernel(PfDownArgs a) {
 
 // y[i] = bf16(sum of the S <= kDownSlicesMax partials, in slice order), four
 // outputs per thread with 16-byte loads (n % 4 == 0).
-constexpr int kDownSlicesMax = 8;
 __global__ void pf_down_reduce_kernel(const float* part, uint16_t* y, long n, int S) {
     const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= n)
@@ -525,39 +524,26 @@ hipError_t launch_prefill_lora(const uint16_t* Ag, const uint16_t* Au, const uin
     return hipGetLastError();
 }
 
-constexpr int kPfCus = 256;        // compute units of an MI355X
+// Compute units of the plans (without a device, whose launches fail anyway,
+// those of a whole MI355X).
+static int plan_cus() {
+    const int n = device_cus();
+    return n > 0 ? n : 256;
+}
 
-// Token tile of the down kernel: 256 tokens (8 waves; every
-// dequantized weight serves 256 tokens) where M allows, else 128 (4 waves).
-int prefill_bm(int M) { return M % 256 == 0 ? 256 : 128; }
 hipError_t launch_prefill_gateup(const uint32_t* cg, const uint32_t* mg, const uint32_t* cu,
                                  const uint32_t* mu, const uint16_t* x, const uint16_t* T,
                                  const uint16_t* Bg, const uint16_t* Bu, uint16_t* h, int M, int d,
                                  int f, int g, int r, hipStream_t st) {
     PfGateUpArgs a{cg, mg, cu, mu, x, T, Bg, Bu, h, M, d, f, g, r};
-    // Three tiles: 256 tokens x 128 columns of h and 256 x 64 (one workgroup per
-    // compute unit), 128 x 64 (two; the only one for an odd number of 128-token
-    // tiles).  A larger tile moves less through LDS per matrix instruction but
-    // leaves more of the chip idle when there are few, so the one whose rounds
-    // over the chip take the least time is used; a round measured 1 : 0.62 :
-    // 0.77 (0.5 where the small tiles get a compute unit each).  4B shape
-    // (d = 2560, f = 9728), whole chunk, us, in that order: M = 256 111, 81,
-    // 93; M = 512 139, 151, 151; M = 1024 258, 241, 248.  20B-class, M = 512:
-    // 358, 383, 433; M = 256: 269, 214, 240.
-    const auto rounds = [&](int bm, int hc, int per_cu) {
-        return (double)(((long)(M / bm) * (f / hc) + per_cu * kPfCus - 1) / (per_cu * kPfCus));
-    };
-    const double c64 = M % 256 == 0 ? 0.62 * rounds(256, 64, 1) : 1e30;
-    const double c128 = M % 256 == 0 && f % 128 == 0 ? rounds(256, 128, 1) : 1e30;
-    const double csmall = (long)(M / 128) * (f / 64) <= kPfCus ? 0.5 : 0.77 * rounds(128, 64, 2);
-    const int HC = c128 <= c64 && c128 <= csmall ? 128 : 64;
-    const int BM = HC == 128 || c64 <= csmall ? 256 : 128;
+    const auto [BM, HC] = prefill_gateup_tile(M, f, plan_cus());
     const size_t lds = (size_t)2 * (BM + 2 * HC) * 8 * 16;
+    const int grid = (M / BM) * (f / HC), threads = 2 * BM;
     auto run = [&](auto k) {
         hipError_t e = set_lds(k, lds);
         if (e != hipSuccess)
             return e;
-        k<<<(M / BM) * (f / HC), 2 * BM, lds, st>>>(a);
+        k<<<grid, threads, lds, st>>>(a);
         return hipGetLastError();
     };
     if (HC == 128)
@@ -565,32 +551,10 @@ hipError_t launch_prefill_gateup(const uint32_t* cg, const uint32_t* mg, const u
     return BM == 256 ? run(pf_gateup_kernel<256, 64, 512, 2>) : run(pf_gateup_kernel<128, 64, 256, 2>);
 }
 
-// The most slices of f a chunk's down half may take (the workspace is sized
-// for them): doubled while under 512 tiles, slices of whole 64-wide steps.
-static int down_slices_most(int M, int d, int f) {
-    const long tiles = (long)(M / prefill_bm(M)) * (d / 128);
-    int S = 1;
-    while (S < kDownSlicesMax && tiles * S < 512 && f % (2 * S * PF_BK) == 0) S *= 2;
-    return S;
-}
-
-// The slices it takes: as many as keep (token tile x row tile x slice) within
-// one round over the compute units (of 128-token workgroups two fit one, and
-// a quarter more than that still pays: M = 640 of the 8B shape 312 us with 640
-// workgroups, 316 with 320).  A second round costs more than the finer
-// slices save, and every slice writes and re-reads its partials: 4B shape,
-// M = 512, 4 slices (160 workgroups) 132 us per chunk, 8 (320) 138; M = 1024, 2
-// (160) 242, 8 260; M = 2048, 1 (160) 390, 4 398; 20B-class, M = 256, 4 (192)
-// 256, 8 269, M = 512, 2 (192) and 8 363.
-int prefill_down_slices(int M, int d, int f) {
-    const long tiles = (long)(M / prefill_bm(M)) * (d / 128);
-    int S = down_slices_most(M, d, f);
-    while (S > 1 && 2 * tiles * S > (prefill_bm(M) == 128 ? 5 : 2) * kPfCus) S /= 2;
-    return S;
-}
+int prefill_down_slices(int M, int d, int f) { return prefill_down_slices(M, d, f, plan_cus()); }
 
 size_t prefill_down_part_bytes(int M, int d, int f) {
-    const int S = down_slices_most(M, d, f);
+    const int S = prefill_down_slices_most(M, d, f);
     return S > 1 ? (size_t)S * M * d * 4 : 0;
 }
 

@@ -1,10 +1,33 @@
 """Helpers shared by the test modules: move seeded workloads to the device,
 pack them with the HIP library, and quantize them with the oracle."""
+import ctypes
+import os
+import subprocess
+
 import numpy as np
 import torch
 
 import oracle as orc
 import workloads as wl
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_04238_amd", "csrc")
+
+
+def host_library(src: str, folder) -> ctypes.CDLL:
+    """C++ that includes the library's host-only headers, compiled with g++."""
+    (folder / "p.cc").write_text(src)
+    subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-std=c++17", "-shared", "-fPIC", "-I", CSRC,
+                    str(folder / "p.cc"), "-o", str(folder / "p.so")], check=True)
+    return ctypes.CDLL(str(folder / "p.so"))
+
+
+PREFILL_PLAN_SRC = """
+#include "prefill_plan.h"
+extern "C" int tile_bm(int M, int f, int cus) { return qmlp::prefill_gateup_tile(M, f, cus).bm; }
+extern "C" int tile_hc(int M, int f, int cus) { return qmlp::prefill_gateup_tile(M, f, cus).hc; }
+extern "C" int slices(int M, int d, int f, int cus) { return qmlp::prefill_down_slices(M, d, f, cus); }
+extern "C" int slices_most(int M, int d, int f) { return qmlp::prefill_down_slices_most(M, d, f); }
+"""
 
 
 def act_tensor(bits: np.ndarray, act: str = "f16", device="cuda") -> torch.Tensor:

@@ -3,14 +3,12 @@ sizes and compute units), compiled here with g++ and checked without a GPU:
 every tile of every block belongs to one workgroup and every step of a row to
 one wave, LDS and the slices' counters suffice, and the chip is used."""
 import ctypes
-import os
 import shutil
-import subprocess
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CSRC = os.path.join(ROOT, "paper_2606_04238_amd", "csrc")
+from qmlp_testutil import host_library
+
 FIELDS = ("kw", "tw", "mw", "tg", "sk", "ns", "wgs", "wpb", "tq", "tr", "sq", "sr", "ipw", "ikw", "pack",
           "threads", "lds")
 
@@ -45,11 +43,7 @@ extern "C" void routed_range(int wg, int wgs, int nv, int tpb, int tw, long* o) 
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    (d / "p.cc").write_text(SRC)
-    subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "p.cc"),
-                    "-o", str(d / "p.so")], check=True)
-    lib = ctypes.CDLL(str(d / "p.so"))
+    lib = host_library(SRC, tmp_path_factory.mktemp("plan"))
 
     def call(which, *args, cus=256):
         out = (ctypes.c_long * len(FIELDS))()
