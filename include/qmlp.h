@@ -132,8 +132,8 @@ size_t qmlp_meta_bytes(int n_out, int k_in, int group);
  * where the block's launches on the matrix cores need more bytes than those,
  * for LoRA-A's slices and the fp32 partial sums [slices][M][d] of long down
  * rows, as many as they need), and on the prefill path, when the down projection splits f into slices
- * to fill the chip, the slices' fp32 partial sums [S][M][d].  qmlp_forward
- * also takes a decode workspace without the bytes for long down rows beyond
+ * to fill the chip, the slices' fp32 partial sums [S][M][d].  The calls
+ * also take a decode workspace without the bytes for long down rows beyond
  * the hand-off words; they then run the stand-alone kernel, which is slower.
  * The workspace must be ZERO before
  * its first call, and zeroed again before it serves a block of another shape

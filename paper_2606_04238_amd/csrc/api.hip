@@ -437,6 +437,13 @@ size_t stack_layer_ws(const qmlp_mlp* layers, int M, qmlp_dtype dtype) {
     return round256(ws_total_bytes(layers, M, dtype));
 }
 
+// A stack's workspace with lws bytes for its blocks.
+size_t stack_bytes(const qmlp_mlp* layers, int M, qmlp_dtype dtype, size_t lws) {
+    return lws + 3 * round256((size_t)M * layers[0].gate.k_in * 2) +
+           (stack_persistent(layers, M, dtype)
+                ? stack_ws_bytes(layers[0].gate.k_in, layers[0].gate.n_out, layers[0].rank) : 0);
+}
+
 // Independent blocks at one token in the W4/W2-GateUp form stream: every
 // batch of up to kBatchMax blocks is the LoRA-A launch, one persistent
 // gate/up launch and one persistent down launch (decode_stream.hip).
@@ -658,7 +665,7 @@ qmlp_status qmlp_gateup_w2_lora(const qmlp_mlp* mlp, const void* x, int M, qmlp_
         return QMLP_ERR_NULL;
     if (!aligned16(x) || !aligned16(h))
         return QMLP_ERR_ALIGN;
-    if (!ws || ws_bytes < qmlp_workspace_bytes(mlp, M, dtype))
+    if (!ws || ws_bytes < ws_least_bytes(mlp, M, dtype))
         return QMLP_ERR_WORKSPACE;
     if (!aligned16(ws))
         return QMLP_ERR_ALIGN;
@@ -768,10 +775,7 @@ int qmlp_forward_launches(const qmlp_mlp* mlp, int M, qmlp_dtype dtype) {
 size_t qmlp_stack_workspace_bytes(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
     if (check_stack(layers, L, M, dtype) != QMLP_OK || M == 0)
         return 0;
-    size_t n = stack_layer_ws(layers, M, dtype) + 3 * round256((size_t)M * layers[0].gate.k_in * 2);
-    if (stack_persistent(layers, M, dtype))
-        n += stack_ws_bytes(layers[0].gate.k_in, layers[0].gate.n_out, layers[0].rank);
-    return n;
+    return stack_bytes(layers, M, dtype, stack_layer_ws(layers, M, dtype));
 }
 
 size_t qmlp_stack_error_offset(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
@@ -802,13 +806,15 @@ qmlp_status qmlp_forward_stack(const qmlp_mlp* layers, int L, const void* x, int
         return QMLP_ERR_NULL;
     if (!aligned16(x) || !aligned16(y) || (x_out && !aligned16(x_out)))
         return QMLP_ERR_ALIGN;
-    if (!ws || ws_bytes < qmlp_stack_workspace_bytes(layers, L, M, dtype))
+    size_t lws = stack_layer_ws(layers, M, dtype);
+    if (ws_bytes < stack_bytes(layers, M, dtype, lws))       // as qmlp_forward: the least serves
+        lws = round256(ws_least_bytes(layers, M, dtype));
+    if (!ws || ws_bytes < stack_bytes(layers, M, dtype, lws))
         return QMLP_ERR_WORKSPACE;
     if (!aligned16(ws))
         return QMLP_ERR_ALIGN;
     const int d = layers[0].gate.k_in;
     const size_t step = (size_t)M * d * 2;
-    const size_t lws = stack_layer_ws(layers, M, dtype);
     char* pp[2] = {static_cast<char*>(ws) + lws, static_cast<char*>(ws) + lws + round256(step)};
     uint16_t* ub = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + lws + 2 * round256(step));
     char* area = static_cast<char*>(ws) + lws + 3 * round256(step);

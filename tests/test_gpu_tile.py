@@ -180,6 +180,20 @@ def test_partial_sums_get_their_workspace(q, M):
     assert orc.max_rel_err(values_of(y), want) <= 1e-2
     assert torch.equal(q.forward(m, x, ws=ws), y) and not bool(ws[head:].any())
     assert orc.max_rel_err(values_of(q.forward_noalloc(m, x)), want) <= 1e-2
+    # what sufficed without them still does, for a block, its gate/up half and a stack
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    least = head + cus * 256 * 8 + r256(4 * f * 4)
+    small = torch.zeros(least, dtype=torch.uint8, device="cuda")
+    assert orc.max_rel_err(values_of(q.forward(m, x, ws=small)), want) <= 1e-2
+    q.gateup_w2_lora(m, x, ws=small)
+    with pytest.raises(q.QmlpError):
+        q.forward(m, x, ws=small[:-256])
+    st, more = q.Stack([m, m]), 3 * r256(M * d * 2)
+    ref_y = q.forward_stack(st, x, ws=q.stack_workspace(st, M))
+    some_y = q.forward_stack(st, x, ws=torch.zeros(least + more, dtype=torch.uint8, device="cuda"))
+    assert orc.max_rel_err(values_of(some_y), values_of(ref_y)) <= 2e-3
+    with pytest.raises(q.QmlpError):
+        q.forward_stack(st, x, ws=torch.zeros(least + more - 256, dtype=torch.uint8, device="cuda"))
 
 
 @pytest.mark.parametrize("d,f,gb,g,db,r,E,k,M,same", [
