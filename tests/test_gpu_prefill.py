@@ -18,7 +18,8 @@ import torch
 
 import oracle as orc
 import workloads as wl
-from qmlp_testutil import act_tensor, bits_of, gpu_mlp, oracle_forward, oracle_q, values_of
+from qmlp_testutil import (PREFILL_PLAN_SRC, act_tensor, bits_of, gpu_mlp, host_library, oracle_forward, oracle_q,
+                           values_of)
 
 pytestmark = pytest.mark.gpu
 
@@ -39,14 +40,23 @@ def _announce(*what):
     print("\n[case]", *what, flush=True)
 
 
-def _down_slices(M, d, f):
-    """Slices of f the chunk's down projection takes (the library's rule:
-    double while under 512 token x row tiles and f stays whole 128-wide
-    steps per slice, at most 8)."""
-    S = 1
-    while S < 8 and (M // 128) * (d // 128) * S < 512 and f % (2 * S * 64) == 0:
-        S *= 2
-    return S
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """The library's own rules for the tile and the slices, on this device."""
+    lib = host_library(PREFILL_PLAN_SRC, tmp_path_factory.mktemp("plan"))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    class Plan:
+        whole_chip = cus == 256
+
+        @staticmethod
+        def tile(M, f):
+            return lib.tile_bm(M, f, cus), lib.tile_hc(M, f, cus)
+
+        @staticmethod
+        def slices(M, d, f):
+            return lib.slices(M, d, f, cus)
+    return Plan
 
 
 PREFILL_CASES = {
@@ -60,11 +70,24 @@ PREFILL_CASES = {
                                   act="bf16"),
     "pf_m384_r32_g128_out": wl.Config("pf_m384_r32_g128_out", M=384, d=768, f=1024, g=128, r=32,
                                       L=1, act="bf16", outliers=True),
-    # 256-token tiles with 128 columns of h per block (f % 128 == 0), two
-    # token tiles, down over slices of f
+    # f % 128 == 0 at four 128-token tiles, down over slices of f
     "pf_m512_r16_g128_wide": wl.Config("pf_m512_r16_g128_wide", M=512, d=512, f=768, g=128, r=16,
                                        L=1, act="bf16"),
+    # long enough rows of tiles for the larger ones: 256 tokens x 64 columns
+    # of h, and 256 x 128 at two token tiles
+    "pf_m256_r8_g64_long": wl.Config("pf_m256_r8_g64_long", M=256, d=256, f=8320, g=64, r=8, L=1, act="bf16"),
+    "pf_m512_r32_g128_long": wl.Config("pf_m512_r32_g128_long", M=512, d=256, f=8320, g=128, r=32, L=1,
+                                       act="bf16"),
 }
+# the gate/up tile each case runs on 256 compute units (tokens, columns of h)
+PREFILL_TILES = {"pf_m256_r8_g64_long": (256, 64), "pf_m512_r32_g128_long": (256, 128)}
+
+
+def test_cases_run_every_gateup_tile(plan):
+    if not plan.whole_chip:
+        pytest.skip("the cases are made for 256 compute units")
+    tiles = {name: plan.tile(c.M, c.f) for name, c in PREFILL_CASES.items()}
+    assert tiles == {name: PREFILL_TILES.get(name, (128, 64)) for name in PREFILL_CASES}
 
 
 @pytest.mark.parametrize("name", sorted(PREFILL_CASES))
@@ -84,12 +107,12 @@ def test_prefill_gateup_matches_oracle(q, name):
 
 
 @pytest.mark.parametrize("name", sorted(PREFILL_CASES))
-def test_prefill_forward_matches_oracle(q, name):
+def test_prefill_forward_matches_oracle(q, plan, name):
     cfg = PREFILL_CASES[name]
     _announce("prefill forward", name, "M", cfg.M, "d", cfg.d, "f", cfg.f, "g", cfg.g, "r", cfg.r)
     L = wl.layer(cfg, 0)
     mlp = gpu_mlp(L)
-    S = _down_slices(cfg.M, cfg.d, cfg.f)
+    S = plan.slices(cfg.M, cfg.d, cfg.f)
     assert q.forward_launches(mlp, cfg.M, torch.bfloat16) == 4 + (S > 1)
     print("down slices", S)
     y = q.forward(mlp, act_tensor(L.x, "bf16"))
@@ -114,12 +137,12 @@ def test_prefill_down_alone_matches_oracle_on_same_h(q):
     assert err <= Y_TOL
 
 
-def test_prefill_without_adapter(q):
+def test_prefill_without_adapter(q, plan):
     cfg = PREFILL_CASES["pf_m128_r8_g64"]
     _announce("prefill rank 0", cfg.name)
     L = wl.layer(cfg, 0)
     mlp = gpu_mlp(L, rank=False)
-    assert q.forward_launches(mlp, cfg.M, torch.bfloat16) == 2 + (_down_slices(cfg.M, cfg.d, cfg.f) > 1)
+    assert q.forward_launches(mlp, cfg.M, torch.bfloat16) == 2 + (plan.slices(cfg.M, cfg.d, cfg.f) > 1)
     y = q.forward(mlp, act_tensor(L.x, "bf16"))
     torch.cuda.synchronize()
     y_ref, _ = oracle_forward(L, rank=False)
@@ -157,9 +180,9 @@ def test_prefill_deterministic_and_tiles_independent(q):
     assert torch.equal(y1[128:].view(torch.int16), y3.view(torch.int16))
 
 
-def test_prefill_full_size_sampled_tokens(q):
+def test_prefill_full_size_sampled_tokens(q, plan):
     """The 20B-width prefill chunk (M=512, d=6144, f=16384, g128, r32) in the
-    launch configuration the benchmark times (down over four slices of f);
+    launch configuration the benchmark times (down over two slices of f);
     the oracle computes one sampled token of every 128-token tile (rows are
     independent)."""
     cfg = wl.CONFIGS["prefill20b"]
@@ -168,7 +191,8 @@ def test_prefill_full_size_sampled_tokens(q):
     mlp = gpu_mlp(L)
     y = q.forward(mlp, act_tensor(L.x, "bf16"))
     torch.cuda.synchronize()
-    assert _down_slices(cfg.M, cfg.d, cfg.f) == 4
+    if plan.whole_chip:
+        assert plan.tile(cfg.M, cfg.f) == (256, 128) and plan.slices(cfg.M, cfg.d, cfg.f) == 2
     rows = [0, 211, 300, 511]
     yv = values_of(y, "bf16")[rows]
     y_ref, _ = oracle_forward(L, x=np.ascontiguousarray(L.x[rows]))
