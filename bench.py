@@ -887,7 +887,7 @@ def main(argv=None):
             "mode": "hip_graph" if args.mode == "graph" else "eager",
             "path": {"streamed": "streamed launches (gate/up with LoRA-A, then down, over every block)",
                      "mfma": "matrix-core launches (LoRA-A, gate/up, down over every block)",
-                     "batched": "batched stand-alone kernels"}[path],
+                     "batched": "batched launches, each half on the matrix cores or the stand-alone kernels"}[path],
             "eager_us_per_mlp_step": round(eager_step * 1e3 / L, 3),
             "graph_us_per_mlp_step": round(graph_step * 1e3 / L, 3),
             "median_ms_per_step_with_per_step_events": round(statistics.median(head), 4),

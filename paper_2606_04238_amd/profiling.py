@@ -72,26 +72,43 @@ def _counter_means(pmc_dir):
     return name, out, rows
 
 
+def _grid(row):
+    """Work-items of a dispatch (0 where the rows do not say)."""
+    if "Grid_Size" in row:
+        return int(row["Grid_Size"])
+    if "Grid_Size_X" in row:
+        return int(row["Grid_Size_X"]) * int(row["Grid_Size_Y"]) * int(row["Grid_Size_Z"])
+    return 0
+
+
 def step_dispatches(rows, parts, name_key):
     """Dispatch ids of the step's launches, one list per part: every run of
     consecutive dispatches (in dispatch order) whose kernel names contain
     parts[0], parts[1], ... in turn.  A command may launch the same kernel
     outside the step (one block per call, other precisions); those
-    dispatches do not follow the step's order and are left out.  None when
-    the rows carry no dispatch ids or no such run exists."""
+    dispatches do not follow the step's order and are left out, or follow it
+    on smaller grids: of runs that differ in kernels or grids those with the
+    most work-items count.  None when the rows carry no dispatch ids or no
+    such run exists; two kinds of run of one size are an error."""
     if not rows or "Dispatch_Id" not in rows[0]:
         return None
-    seq = sorted({int(r["Dispatch_Id"]): r[name_key] for r in rows}.items())
-    out = [[] for _ in parts]
+    seq = sorted({int(r["Dispatch_Id"]): (r[name_key], _grid(r)) for r in rows}.items())
+    kinds = {}
     i = 0
     while i + len(parts) <= len(seq):
-        if all(parts[j] in seq[i + j][1] for j in range(len(parts))):
-            for j in range(len(parts)):
-                out[j].append(seq[i + j][0])
+        run = seq[i:i + len(parts)]
+        if all(part in name for part, (_, (name, _)) in zip(parts, run)):
+            kinds.setdefault(tuple(k for _, k in run), []).append([n for n, _ in run])
             i += len(parts)
         else:
             i += 1
-    return out if out[0] else None
+    if not kinds:
+        return None
+    size = {k: sum(g for _, g in k) for k in kinds}
+    most = [k for k in kinds if size[k] == max(size.values())]
+    if len(most) != 1:
+        raise ValueError("%d kinds of launches match %r" % (len(most), parts))
+    return [list(ids) for ids in zip(*kinds[most[0]])]
 
 
 def _part_values(rows, per, parts):
@@ -148,26 +165,27 @@ def summarize(kt_dir, pf_dir, pw_dir, kernel, copy_mib, out_md, commands, stream
     # `kernel` may name several launches of one step, joined by "|": the
     # step's duration and bytes are the sums of their per-dispatch means
     parts = kernel.split("|")
-    krows = []
-    for part in parts:
-        rows = [r for r in stats if part in r["Name"]]
-        if not rows:
-            raise ValueError("kernel %r matches no row of the stats" % part)
-        # several instantiations (other calls of the run): the step's is the longest in sum
-        krows.append(dict(max(rows, key=lambda r: float(r["Calls"]) * float(r["AverageNs"]))))
     # with the per-dispatch trace, the step's own dispatches give the figures
+    ids, dur, name = None, {}, {}
     traces = glob.glob(os.path.join(kt_dir, "*kernel_trace.csv"))
     if len(traces) == 1:
         trows = list(csv.DictReader(open(traces[0])))
         ids = step_dispatches(trows, parts, "Kernel_Name")
+        for r in trows:
+            dur[int(r["Dispatch_Id"])] = int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
+            name[int(r["Dispatch_Id"])] = r["Kernel_Name"]
+    krows = []
+    for i, part in enumerate(parts):
+        rows = [r for r in stats if part in r["Name"]]
+        if ids is not None:                     # of several instantiations, the step's
+            own = {name[k] for k in ids[i]}
+            rows = [r for r in rows if r["Name"] in own]
+        if len(rows) != 1:
+            raise ValueError("kernel %r matches %d rows of the stats" % (part, len(rows)))
+        krows.append(dict(rows[0]))
         if ids is not None:
-            dur = {int(r["Dispatch_Id"]): int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
-                   for r in trows}
-            name = {int(r["Dispatch_Id"]): r["Kernel_Name"] for r in trows}
-            for kr, idl in zip(krows, ids):
-                ns = [dur[i] for i in idl]
-                kr.update(Name=name[idl[0]], Calls=len(ns), AverageNs=statistics.mean(ns), MinNs=min(ns),
-                          MaxNs=max(ns))
+            ns = [dur[k] for k in ids[i]]
+            krows[-1].update(Calls=len(ns), AverageNs=statistics.mean(ns), MinNs=min(ns), MaxNs=max(ns))
     avg_us = sum(float(r["AverageNs"]) for r in krows) / 1e3
     copy_kib = copy_mib * 1024.0
     stream_kib = stream_mib * 1024.0

@@ -2,6 +2,8 @@
 is read back only for the kernel and the sources that were profiled."""
 import os
 
+import pytest
+
 from paper_2606_04238_amd import profiling
 
 
@@ -76,6 +78,29 @@ def test_step_dispatches_follow_the_launch_order():
     assert profiling.step_dispatches(rows, ["a_kernel", "b_kernel"], "Kernel_Name") == [[1, 5], [2, 6]]
     assert profiling.step_dispatches(rows, ["c_kernel", "b_kernel"], "Kernel_Name") is None
     assert profiling.step_dispatches([{"Kernel_Name": "a"}], ["a"], "Kernel_Name") is None
+
+
+def test_step_dispatches_are_those_of_the_batched_call():
+    """The same kernels in the same order on one block and on a batch: the
+    batch's launches (more work-items) are the step; kinds of one size, which
+    nothing tells apart, are an error and not one of them."""
+    def rows(*launches):
+        return [{"Dispatch_Id": str(i + 1), "Kernel_Name": n, "Grid_Size_X": str(g), "Grid_Size_Y": "2",
+                 "Grid_Size_Z": "1"} for i, (n, g) in enumerate(launches)]
+    one, batch = [("a<1>", 256), ("b<1>", 512)], [("a<1>", 9216), ("b<1>", 512)]
+    assert profiling.step_dispatches(rows(*one, *batch, *one, *batch), ["a<", "b<"], "Kernel_Name") == [[3, 7], [4, 8]]
+    with pytest.raises(ValueError):
+        profiling.step_dispatches(rows(*batch, ("a<1>", 9216), ("b<2>", 512)), ["a<", "b<"], "Kernel_Name")
+
+
+def test_ambiguous_kernel_is_an_error_without_a_trace(tmp_path):
+    """Two instantiations match and nothing tells which is the step's."""
+    kt = tmp_path / "kt"
+    kt.mkdir()
+    _csv(kt / "x_kernel_stats.csv", ["Name", "Calls", "AverageNs", "MinNs", "MaxNs", "Percentage"],
+         [["void a_kernel<1>()", 3, 700.0, 100, 1000, 50], ["void a_kernel<2>()", 2, 3000.0, 3000, 3000, 50]])
+    with pytest.raises(ValueError):
+        profiling.summarize(str(kt), str(kt), str(kt), "a_kernel", 1, str(tmp_path / "s.md"), ["cmd"])
 
 
 def test_summary_takes_the_step_dispatches_from_the_trace_and_counters(tmp_path):
