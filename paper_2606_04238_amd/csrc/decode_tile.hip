@@ -818,6 +818,14 @@ hipError_t launch_lora_a_tile(const BatchArgs& b, int nb, int slices, hipStream_
     return hipGetLastError();
 }
 
+// Register sets of the gate/up half where gate and up have waves of their own:
+// 2-bit groups of 32 hold sixteen groups' (scale | zero) words a step, and a
+// fourth set spills (1 to 4 registers; 36 blocks of d = 2560, f = 9728 at 5
+// tokens 305.5 us with four sets, 302 with three; 4 at 16 66.0 and 64.1).
+// In turn, gate and up take an even number: four sets, of which only the
+// routed instance of those groups spills (3 registers).
+constexpr int gu_sets(int bits, int g) { return bits == 2 && g == 32 ? 3 : 4; }
+
 hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scratch, hipStream_t st) {
     TilePlan p;
     if (!plan_gateup(b.M, b.d, b.f, b.gg, b.bg, b.r, nb, b.route != nullptr, device_cus(), p))
@@ -825,7 +833,7 @@ hipError_t launch_gateup_tile(const BatchArgs& b, int nb, int slices, float* scr
     p.ts = slices;
 #define QMLP_TGU_R(B_, G_, R_)                                                            \
     if (b.bg == B_ && b.gg == G_ && (b.route != nullptr) == R_)                           \
-        return p.mw == 2 ? tile_run(tile_kernel<B_, G_, true, 1, 1, false, R_, 4>, b, nb, p, scratch, st) \
+        return p.mw == 2 ? tile_run(tile_kernel<B_, G_, true, 1, 1, false, R_, gu_sets(B_, G_)>, b, nb, p, scratch, st) \
                          : tile_run(tile_kernel<B_, G_, true, 2, 1, false, R_, 4>, b, nb, p, scratch, st);
 #define QMLP_TGU(B_, G_) QMLP_TGU_R(B_, G_, false) QMLP_TGU_R(B_, G_, true)
     QMLP_TGU(2, 128) QMLP_TGU(2, 64) QMLP_TGU(2, 32) QMLP_TGU(4, 128) QMLP_TGU(4, 64) QMLP_TGU(4, 32)
