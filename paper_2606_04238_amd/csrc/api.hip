@@ -487,26 +487,23 @@ bool layers_batched(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
 // they take a half, the stand-alone ones otherwise.
 enum class BatchPath { kBatched, kStreamed, kMfma, kTile };
 
-// The tile kernels come before those of decode_mfma.hip where they take both
-// halves (us, those and these): 36 Qwen3-8B-shaped blocks at M = 4 and 16 450
-// and 403, 508 and 469, in groups of 64 at M = 8 541 and 473; ten 14B-class ones
-// (d = 5120, f = 17408, groups of 64) at M = 8 320 and 276, 40 in groups of 128
-// 888 and 871.  Only where the start-up no longer counts, a tile's gate and up
-// run in turn over more than eight steps, down runs in slices and groups of 64
-// double the corrections, do those stay ahead: 20 such 14B-class blocks 524 and
-// 528, 40 of them 969 and 986, at M = 4 936 and 970.  Rows too long for the tile
-// kernels stay there as well.
-constexpr long kMfmaWeights = 1800000000;
+// The tile kernels come before those of decode_mfma.hip wherever they take both
+// halves; those keep the rows too long for them (up to eight tokens: more are
+// past their own LDS).  us, those and these: 36 Qwen3-8B-shaped blocks at M = 4
+// 450 and 403, in groups of 64 at M = 8 541 and 473; 14B-class ones (d = 5120,
+// f = 17408, groups of 64) at M = 8 ten 320 and 276, 28 737 and 713.  The
+// largest batches in groups of 64 gain or lose a few percent either way, and no
+// rule of sizes held over them: 40 of d = 5120 971 and 997, 40 of d = 4608, f = 14336 743 and 766
+// (36 at M = 16 727 and 759), 32 of d = 5120, f = 13824 at M = 6 612 and 625; 40 of
+// d = 5632, f = 16384 991 and 962, 40 of d = 6144 1124 and 1037.
 BatchPath batch_path(const qmlp_mlp* layers, int L, int M, qmlp_dtype dtype) {
     const int n = L < kBatchMax ? L : kBatchMax;
     if (layers_streamed(layers, L, M, dtype))
         return BatchPath::kStreamed;
-    if (!layers_mfma(layers, L, M, dtype))
+    if (M > 8 || !layers_mfma(layers, L, M, dtype) ||
+        (tile_gateup(layers, M, n) && tile_slices(&layers[0].down, M, n) > 0))
         return BatchPath::kTile;
-    const qmlp_qweight& w = layers[0].gate;
-    const int sk = tile_slices(&layers[0].down, M, n);
-    const bool late = w.group == 64 && w.k_in > 8 * 512 && sk > 1 && (long)n * w.n_out * w.k_in >= kMfmaWeights;
-    return tile_gateup(layers, M, n) && sk > 0 && !late ? BatchPath::kTile : BatchPath::kMfma;
+    return BatchPath::kMfma;
 }
 
 // t of a batch: [nb][M][2r] fp32, kLoraSlices such arrays of partial sums on

@@ -1,4 +1,4 @@
-// Decode at several tokens (3 <= M <= 16, binary16) on the matrix cores,
+// Decode at several tokens (3 <= M <= 8, binary16) on the matrix cores,
 // gfx950: a batch of independent blocks as two persistent launches after the
 // LoRA-A products,
 //
@@ -7,10 +7,9 @@
 //   down launch:     y_l = W4down h_l (Sec. 3.3).
 //
 // Taken for the batches whose rows the tile kernels (decode_tile.hip) do not
-// hold (gate/up rows past 6144 codes, or down rows past their slices), and for
-// large batches of long rows in groups of 64, where these are ahead (40 blocks
-// of d = 5120, f = 17408 at 8 tokens: 969 us here, 986 there; 36 of d = 4096,
-// f = 12288: 541 and 473).
+// hold (gate/up rows past 6144 codes), which are slower where those take them
+// (36 blocks of d = 4096, f = 12288 in groups of 64 at 8 tokens: 541 us here,
+// 473 there).
 //
 // With M tokens a weight feeds M multiply-adds; on the vector ALU that is
 // M/2 dot2 operations per weight on top of its dequantization, more than the
@@ -41,7 +40,7 @@
 // Work split.  Each workgroup owns a contiguous range of the batch's
 // 16-row items (flattened over blocks).
 //   gate/up: the whole x' of the block an item belongs to sits in LDS (MT
-//     token rows, MT = 4, 8 or 16 >= M; A rows past MT re-read token
+//     token rows, MT = 4 or 8 >= M; A rows past MT re-read token
 //     row & (MT - 1), their results are never stored); a range touching two
 //     blocks stages them one after the other.  Waves take the range's items
 //     in turn and stream each item's codes in steps of four groups with two
@@ -661,6 +660,8 @@ int mf_grid(long items) {
 
 }  // namespace
 
+// The form and its LDS at up to 16 tokens (the matrix-core form that
+// qmlp_layers_path reports); the launches below run up to 8 of them.
 bool mfma_supported(int M, int d, int f, int gg, int bg, int gd, int bd, int r, int nb) {
     if (M < 3 || M > 16 || bg != 2 || bd != 4 || (gg != 64 && gg != 128) || (gd != 64 && gd != 128))
         return false;
@@ -675,7 +676,7 @@ bool mfma_supported(int M, int d, int f, int gg, int bg, int gd, int bd, int r, 
 }
 
 hipError_t launch_lora_a_mfma(const BatchArgs& b, int nb, hipStream_t st) {
-    if (!mfma_supported(b.M, b.d, b.f, b.gg, b.bg, b.gd, b.bd, b.r, nb) || b.r == 0)
+    if (b.M > 8 || !mfma_supported(b.M, b.d, b.f, b.gg, b.bg, b.gd, b.bd, b.r, nb) || b.r == 0)
         return hipErrorInvalidValue;
     mf_lora_kernel<<<dim3((unsigned)(2 * b.r / 16 * kLoraSlices), (unsigned)nb), 256, 0, st>>>(b, nb);
     return hipGetLastError();
@@ -691,13 +692,12 @@ hipError_t launch_lora_a_mfma(const BatchArgs& b, int nb, hipStream_t st) {
     }
 
 hipError_t launch_gateup_mfma(const BatchArgs& b, int nb, hipStream_t st) {
-    if (!mfma_supported(b.M, b.d, b.f, b.gg, b.bg, b.gd, b.bd, b.r, nb))
+    if (b.M > 8 || !mfma_supported(b.M, b.d, b.f, b.gg, b.bg, b.gd, b.bd, b.r, nb))
         return hipErrorInvalidValue;
     const int MT = mf_mt(b.M);
     const int grid = mf_grid((long)nb * (b.f / 16));
     const size_t lds = mf_gu_lds(b.d, b.gg, MT);
-    QMLP_MFGU(64, 4) QMLP_MFGU(64, 8) QMLP_MFGU(64, 16)
-    QMLP_MFGU(128, 4) QMLP_MFGU(128, 8) QMLP_MFGU(128, 16)
+    QMLP_MFGU(64, 4) QMLP_MFGU(64, 8) QMLP_MFGU(128, 4) QMLP_MFGU(128, 8)
     return hipErrorInvalidValue;
 }
 
@@ -711,14 +711,13 @@ hipError_t launch_gateup_mfma(const BatchArgs& b, int nb, hipStream_t st) {
     }
 
 hipError_t launch_down_mfma(const BatchArgs& b, int nb, hipStream_t st) {
-    if (!mfma_supported(b.M, b.d, b.f, b.gg, b.bg, b.gd, b.bd, b.r, nb))
+    if (b.M > 8 || !mfma_supported(b.M, b.d, b.f, b.gg, b.bg, b.gd, b.bd, b.r, nb))
         return hipErrorInvalidValue;
     const int MT = mf_mt(b.M);
     const int grid = mf_grid((long)nb * (b.d / 16));
     const int ck = mf_dn_chunk(b.f, b.gd, MT);
     const size_t lds = mf_dn_lds(ck, b.gd, MT);
-    QMLP_MFDN(64, 4) QMLP_MFDN(64, 8) QMLP_MFDN(64, 16)
-    QMLP_MFDN(128, 4) QMLP_MFDN(128, 8) QMLP_MFDN(128, 16)
+    QMLP_MFDN(64, 4) QMLP_MFDN(64, 8) QMLP_MFDN(128, 4) QMLP_MFDN(128, 8)
     return hipErrorInvalidValue;
 }
 

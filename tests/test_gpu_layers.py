@@ -277,21 +277,7 @@ def test_layers_streamed_shapes_match_oracle(q, d, f, g, r, L):
     _check(layers, y, rank=r > 0, which=None if L <= 9 else (0, 1, L // 2, L - 2, L - 1))
 
 
-@pytest.mark.parametrize("M,d,f,g,r,L", [
-    (3, 512, 1536, 64, 8, 1),       # the fewest tokens, one block: fewer items than compute units
-    (4, 512, 6400, 128, 16, 3),     # MT = 4: f over two h' chunks of 6144 codes, the second short
-    (5, 1536, 2560, 64, 0, 9),      # MT = 8, no adapter: h' chunks of 1536 codes, the last short
-    (8, 1024, 2048, 128, 32, 40),   # a full batch: ranges straddle blocks
-    (9, 512, 1536, 64, 16, 41),     # MT = 16, two batches
-    (16, 2048, 3072, 64, 8, 6),     # all sixteen token rows
-])
-def test_layers_mfma_shapes_match_oracle(q, M, d, f, g, r, L):
-    """3 <= M <= 16 runs on the matrix cores (LoRA-A, then one gate/up and
-    one down launch per batch): token counts on both sides of each padded
-    tile height (4, 8, 16), groups 64 and 128, ranks 0 to 32, batches from
-    one block to two batches; d from 512 to 2048 gives each LoRA-A wave 1 to
-    4 steps of 32 (a partial group of four at 1536).  Every block against the oracle (sampled for
-    long batches) and against the stand-alone kernels on the same input."""
+def _matrix_core_batch(q, M, d, f, g, r, L):
     cfg = wl.Config("mfma_m%d_%d_%d" % (M, d, f), M=M, d=d, f=f, g=g, r=r, L=L)
     _announce("layers mfma", cfg.name, "g", g, "r", r, "L", L)
     layers, mlps, ls, x = _blocks(q, cfg, L, rank=r > 0)
@@ -312,6 +298,41 @@ def test_layers_mfma_shapes_match_oracle(q, M, d, f, g, r, L):
     y2 = q.forward_layers(ls, x, ws=ws)
     torch.cuda.synchronize()
     assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,d,f,g,r,L", [
+    (3, 512, 1536, 64, 8, 1),       # the fewest tokens, one block: fewer tiles than compute units
+    (4, 512, 6400, 128, 16, 3),     # f past 24 steps of 256 codes: packed steps
+    (5, 1536, 2560, 64, 0, 9),      # no adapter; workgroups of their own for each block
+    (8, 1024, 2048, 128, 32, 40),   # a full batch: ranges straddle blocks
+    (9, 512, 1536, 64, 16, 41),     # two batches
+    (16, 2048, 3072, 64, 8, 6),     # all sixteen token rows
+])
+def test_layers_mfma_shapes_match_oracle(q, M, d, f, g, r, L):
+    """3 <= M <= 16 runs on the matrix cores (LoRA-A, then one gate/up and
+    one down launch per batch), here on the tile kernels: groups 64 and 128,
+    ranks 0 to 32, batches from one block to two batches.  Every block against
+    the oracle (sampled for long batches) and against the stand-alone kernels
+    on the same input."""
+    assert d <= 6144                # twelve steps of 512 codes: a row of a tile workgroup
+    _matrix_core_batch(q, M, d, f, g, r, L)
+
+
+@pytest.mark.parametrize("M,d,f,g,r,L", [
+    (3, 6656, 512, 64, 8, 1),       # padded height 4 of the token rows, fewer items than compute units
+    (4, 6656, 6400, 128, 16, 3),    # f over two h' chunks of 6144 codes, the second short
+    (5, 7168, 2560, 64, 0, 9),      # height 8, no adapter: h' chunks of 1536 codes, the last short
+    (8, 8192, 768, 128, 32, 2),     # all rows of height 8, the widest
+    (4, 6656, 512, 64, 0, 40),      # a full batch: ranges straddle blocks
+    (6, 6656, 512, 128, 16, 41),    # two batches
+])
+def test_layers_long_rows_match_oracle(q, M, d, f, g, r, L):
+    """Gate/up rows past those the tile kernels hold, up to eight tokens: the
+    kernels that keep the activations in LDS, on both sides of each padded
+    tile height (4 and 8), groups 64 and 128, ranks 0 to 32, batches from one
+    block to two batches."""
+    assert d > 6144 and M <= 8
+    _matrix_core_batch(q, M, d, f, g, r, L)
 
 
 @pytest.mark.parametrize("name", ["qwen3_8b_m4", "qwen3_8b_m16", "dense14b_m8"])
