@@ -186,7 +186,8 @@ qmlp_status qmlp_gateup_w2_lora(const qmlp_mlp *mlp, const void *x, int M, qmlp_
 
 /*
  * The 4-bit down projection (Sec. 3.3): y [M][n_out] = W4down h, with
- * h [M][k_in] and y row-major in the activation type.  No workspace.
+ * h [M][k_in] and y row-major in the activation type.  No workspace (longer
+ * rows than those named at qmlp_linear_batch run the stand-alone kernel).
  * Group 32 only on the binary16 decode path.
  */
 qmlp_status qmlp_down_w4(const qmlp_qweight *down, const void *h, int M, qmlp_dtype dtype,
@@ -286,22 +287,24 @@ int qmlp_stack_launches(const qmlp_mlp *layers, int L, int M, qmlp_dtype dtype);
  * products and one persistent down launch, each workgroup owning a
  * contiguous range of the batch's rows flattened over blocks; h of every
  * block passes through the workspace between the two launches.  Every other
- * binary16 batch of two tokens or more runs on the MATRIX CORES where its
- * halves fit (gate/up at 2 or 4 bits with rows of at most twelve steps of
- * 1024/bits codes; any down): the LoRA-A launch (fp32 partial sums over four
- * slices of d, added in slice order by the next launch), then one gate/up
- * launch and one down launch that multiply every unpacked weight into all M
- * tokens with v_mfma_f32_16x16x32_f16; large batches of long rows do so at
- * one token too.  A half that does not fit (3-bit gate/up) and the rest run
- * the stand-alone kernels as qmlp_forward_batch does; bfloat16 runs
- * qmlp_forward once per block.
+ * binary16 batch of two tokens or more runs each half that fits on the MATRIX
+ * CORES: gate/up at 2 bits with d <= 6144 or at 4 bits with d <= 3072, and any
+ * down (one of several slices of f, below, only beside such a gate/up).  The
+ * LoRA-A launch (fp32 partial sums over four slices of d, added in slice order
+ * by the next launch) is followed by one gate/up launch and one down launch
+ * that multiply every unpacked weight into all M tokens with
+ * v_mfma_f32_16x16x32_f16; large batches of long rows do so at one token too,
+ * and W4/W2-GateUp blocks of longer gate/up rows at 3 to 8 tokens on kernels
+ * that keep the activations in LDS.  A half that does not fit (3-bit gate/up,
+ * 4-bit gate/up past 3072) and the rest run the stand-alone kernels as
+ * qmlp_forward_batch does; bfloat16 runs qmlp_forward once per block.
  *
  * ws/ws_bytes: at least qmlp_layers_workspace_bytes(layers, L, M, dtype)
  * (binary16: that of qmlp_forward_batch, with four times its t area on the
  * matrix cores and twice on the streamed path, and on the matrix cores, where
- * rows of down are longer than one workgroup holds -- f > 6144 at 4 bits,
- * 12288 at up to eight tokens -- fp32 partial sums [slices][min(L,40)][M][d]
- * and 1 KB of counters).  On the streamed path with
+ * rows of down are longer than one workgroup holds -- f > 6144, f > 12288 at
+ * up to eight tokens, half of each at 4 bits in groups of 32 -- fp32 partial
+ * sums [slices][min(L,40)][M][d] and 1 KB of counters).  On the streamed path with
  * adapters the gate/up launch also computes LoRA-A and hands t over as
  * tagged words: the control block's word 0 counts the calls and word 160
  * holds sticky error bits (1 = a wait for t gave up), so the workspace must
@@ -359,9 +362,11 @@ qmlp_status qmlp_forward_batch(const qmlp_mlp *layers, int L, const void *x, int
  * a decoder layer (q, k and v as one [q+2kv][d] matrix, o) and the LM head.
  * w[0..L-1] are host descriptors of one shape [n][k] and width (4, or 2 with
  * group 64/128), 1 <= L <= 40; x [L][M][k] and y [L][M][n] binary16,
- * 1 <= M <= 16 (M == 0 is a no-op).  One launch over the batch (from two
- * tokens on the matrix cores where a row fits one workgroup, else the
- * stand-alone down kernel); no workspace.  n % 64 == 0, k % 64 == 0.
+ * 1 <= M <= 16 (M == 0 is a no-op).  One launch over the batch, no workspace:
+ * from two tokens on the matrix cores where a row fits one workgroup (k <=
+ * 6144, k <= 12288 at up to eight tokens, half of each at 4 bits in groups of
+ * 32), else the stand-alone down kernel, which at several tokens takes
+ * several times as long.  n % 64 == 0, k % 64 == 0.
  */
 qmlp_status qmlp_linear_batch(const qmlp_qweight *w, int L, const void *x, int M,
                               qmlp_dtype dtype, void *y, qmlp_stream stream);

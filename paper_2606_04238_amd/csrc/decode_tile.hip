@@ -1,7 +1,7 @@
-// Decode at several tokens (M <= 16, binary16) on the matrix cores for every
-// shape, group and code width of the stand-alone kernels, gfx950: the
-// gate/up half (Sec. 3.1 Eq. (1), Sec. 3.3, Sec. 4.2, Sec. 5) and any
-// quantized linear (Sec. 3.3).
+// Decode at several tokens (M <= 16, binary16) on the matrix cores at every
+// group of 2- and 4-bit codes, gfx950: the gate/up half with rows of at most
+// twelve steps (2 bits d <= 6144, 4 bits d <= 3072; Sec. 3.1 Eq. (1), Sec. 3.3,
+// Sec. 4.2, Sec. 5) and any quantized linear (Sec. 3.3).
 //
 // What bounds it.  On the vector ALU a weight costs M/2 dot2 operations on
 // top of its unpacking, so from a few tokens on the stand-alone kernels are
@@ -268,8 +268,10 @@ struct TileW {
 };
 
 // Loads of one step of the 16 rows that start at byte offsets co / mo of the
-// code and metadata arrays (kPastEnd: nothing): ol / ml are the lane's offsets
-// for the step (lane_offsets), rb8 the bytes of eight rows.
+// code and metadata arrays: ol / ml are the lane's offsets for the step, rb8
+// the bytes of eight rows.  co and mo of kPastEnd (no such tile), or ol (no
+// such step or unit), load zeros; both together wrap to the first lines of
+// the array, in range, for a tile whose sums nobody adds.
 template <int B, int G>
 __device__ __forceinline__ void w_load(TileW<B, G>& w, Rsrc rc, Rsrc rm, uint32_t ol, uint32_t ml, uint32_t rb8,
                                        uint32_t co, uint32_t mo) {
