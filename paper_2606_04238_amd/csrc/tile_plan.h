@@ -148,7 +148,13 @@ inline bool plan_gateup(int M, int d, int f, int g, int bits, int r, int nb, boo
 inline int linear_spw(int g, int bits) { return bits == 4 && g != 32 ? 2 : 1; }
 
 // Any linear [n][k]: as few slices of k as fit the workgroup's registers, with
-// packed steps where that saves slices.
+// packed steps where that saves slices, and for rows past sixteen steps where
+// a workgroup has one tile at most: then half the waves stage and meet, and
+// nothing streams that they could share (us, unpacked and packed, one matrix
+// of 2048 rows in groups of 128: k = 5120 at 2, 4 and 8 tokens 7.7, 8.0, 8.8
+// and 6.6, 7.2, 7.9, k = 4608 at 2 7.2 and 6.8; past a tile per compute unit
+// both the same or the stream counts, and rows of sixteen steps and fewer
+// start as fast either way).
 inline bool plan_linear(int M, int n, int k, int g, int bits, int nb, bool routed, int cus, TilePlan& p) {
     if (cus <= 0 || M < 1 || M > 16 || nb < 1 || nb > kTileBatch || k % 64 != 0 || n % 16 != 0 || k % g != 0 ||
         (bits != 2 && bits != 4) || (bits == 2 && g == 32) || (long)n * k * bits / 8 >= (1l << 31) ||
@@ -156,7 +162,8 @@ inline bool plan_linear(int M, int n, int k, int g, int bits, int nb, bool route
         return false;
     const int cps = 1024 / bits, spw = linear_spw(g, bits);
     p.ns = (k + cps - 1) / cps;
-    p.pack = M <= 8 && p.ns > kTileWaves * spw ? 1 : 0;
+    const bool few = spw == 2 && p.ns > 8 * spw && (long)nb * (n / 16) <= cus;
+    p.pack = M <= 8 && (p.ns > kTileWaves * spw || few) ? 1 : 0;
     const int per = spw << p.pack;                         // steps per wave
     p.sk = (p.ns + kTileWaves * per - 1) / (kTileWaves * per);
     if ((long)p.sk * nb * M * n * 4 >= (1l << 31) || p.sk > cus)

@@ -45,6 +45,9 @@ SHAPES = [  # d, f, gate bits, group, down bits, group, rank
     (1152, 7040, 4, 32, 2, 128, 16),       # 4-bit group 32 gate/up, 2-bit down in two slices
     (640, 13312, 2, 128, 2, 64, 8),        # three K slices at 2 bits
     (1280, 3200, 3, 32, 4, 64, 8),         # 3-bit gate/up (stand-alone) with a tile down
+    (1024, 4608, 2, 32, 4, 128, 16),       # gate/up stand-alone at two tokens only; packed down
+    (512, 4672, 2, 64, 4, 64, 0),          # ragged packed down of nineteen steps, no adapters
+    (2048, 448, 2, 64, 2, 64, 8),          # one-step down: stand-alone at two tokens only
 ]
 
 
@@ -119,9 +122,11 @@ def test_one_token_batches_match_blocks(q, L, shape):
     assert torch.equal(q.forward_layers(layers, x, ws=ws), y)
 
 
-@pytest.mark.parametrize("M", [2, 9, 16])
+@pytest.mark.parametrize("M", [2, 8, 9, 16])
 @pytest.mark.parametrize("n,k,bits,g,L", [(64, 64, 4, 64, 1), (192, 320, 4, 32, 3), (1088, 2560, 4, 128, 5),
-                                          (320, 4096, 2, 64, 2), (17408, 1024, 4, 128, 1), (128, 6144, 4, 64, 40)])
+                                          (320, 4096, 2, 64, 2), (17408, 1024, 4, 128, 1), (128, 6144, 4, 64, 40),
+                                          (192, 5888, 4, 128, 2), (4096, 4160, 4, 64, 1), (4160, 4160, 4, 64, 1),
+                                          (1024, 512, 2, 128, 1), (1024, 512, 2, 64, 12)])
 def test_linear_matches_oracle(q, n, k, bits, g, L, M):
     print("tile linear", n, k, bits, g, "L", L, "M", M, flush=True)
     rng = np.random.default_rng([n, k, M])
@@ -133,6 +138,27 @@ def test_linear_matches_oracle(q, n, k, bits, g, L, M):
     for l in sorted({0, L // 2, L - 1}):
         want = orc.down(orc.quantize(Ws[l % len(Ws)], bits, g), xb[l].astype(np.float64))
         assert orc.max_rel_err(values_of(y[l]), want) <= 2e-3
+
+
+@pytest.mark.parametrize("M", [2, 3, 16])
+@pytest.mark.parametrize("d,f,g,r", [(1024, 4608, 32, 16), (2048, 4224, 64, 8), (1344, 448, 32, 32)])
+def test_gateup_alone_matches_oracle(q, d, f, g, r, M):
+    """The half by itself: LoRA-A's slices lie where the workspace has its own
+    h (the last shape's is too small for them: one slice), behind which it
+    stays zero; more tiles than compute units go stand-alone at two tokens."""
+    cfg = wl.Config("tile_gu", M=M, d=d, f=f, g=g, r=r, L=1)
+    print("tile gateup alone", d, f, g, r, "M", M, flush=True)
+    L = wl.layer(cfg, 0)
+    m, xb, _ = _block(q, cfg, 0, 2, g, 4, 64)
+    ws = q.workspace(m, M)
+    h = q.gateup_w2_lora(m, act_tensor(xb), ws=ws)
+    want = orc.gateup(orc.quantize(L.W_gate, 2, g), orc.quantize(L.W_up, 2, g), L.A_gate, L.B_gate, L.A_up, L.B_up,
+                      xb, lora_scale=0.75)
+    torch.cuda.synchronize()
+    assert orc.max_rel_err(values_of(h), want) <= 2e-3
+    r256 = lambda v: (v + 255) // 256 * 256
+    assert not bool(ws[1024 + r256(M * 2 * r * 4) + r256(M * f * 2):].any())
+    assert torch.equal(q.gateup_w2_lora(m, act_tensor(xb), ws=ws), h)
 
 
 @pytest.mark.parametrize("M", [9, 16])
