@@ -287,8 +287,8 @@ int qmlp_stack_launches(const qmlp_mlp *layers, int L, int M, qmlp_dtype dtype);
  * products and one persistent down launch, each workgroup owning a
  * contiguous range of the batch's rows flattened over blocks; h of every
  * block passes through the workspace between the two launches.  Every other
- * binary16 batch of two tokens or more runs each half that fits on the MATRIX
- * CORES: gate/up at 2 bits with d <= 6144 or at 4 bits with d <= 3072, and any
+ * binary16 batch of two tokens or more (a few short rows at two tokens aside)
+ * runs each half that fits on the MATRIX CORES: gate/up at 2 bits with d <= 6144 or at 4 bits with d <= 3072, and any
  * down (one of several slices of f, below, only beside such a gate/up).  The
  * LoRA-A launch (fp32 partial sums over four slices of d, added in slice order
  * by the next launch) is followed by one gate/up launch and one down launch
@@ -363,8 +363,8 @@ qmlp_status qmlp_forward_batch(const qmlp_mlp *layers, int L, const void *x, int
  * w[0..L-1] are host descriptors of one shape [n][k] and width (4, or 2 with
  * group 64/128), 1 <= L <= 40; x [L][M][k] and y [L][M][n] binary16,
  * 1 <= M <= 16 (M == 0 is a no-op).  One launch over the batch, no workspace:
- * from two tokens on the matrix cores where a row fits one workgroup (k <=
- * 6144, k <= 12288 at up to eight tokens, half of each at 4 bits in groups of
+ * from two tokens on (2-bit rows of k <= 512: mostly from three) on the matrix
+ * cores where a row fits one workgroup (k <= 6144, k <= 12288 at up to eight tokens, half of each at 4 bits in groups of
  * 32), else the stand-alone down kernel, which at several tokens takes
  * several times as long.  n % 64 == 0, k % 64 == 0.
  */

@@ -112,18 +112,48 @@ bool fused_mlp(const qmlp_mlp* mlp, int M) {
 //     500 (f = 2880 65 and 68).
 constexpr long kTileOneToken = 150000000;
 
-// Whether the gate/up half of a batch of nb such blocks takes the tile
-// kernels, and the slices of f its down half takes there (0: stand-alone).
+// At two tokens the stand-alone kernels keep two kinds of short rows, where
+// they start sooner and the tiles leave a last round nearly empty (us,
+// stand-alone and tile):
+//   the 2-bit gate/up half of one block with more tiles than compute units:
+//     d = 1536, f = 8192 in groups of 32, 64 and 128 10.0 and 12.1, 9.8 and 11.3,
+//     9.8 and 10.9; d = 2560, f = 6144 12.2 and 14.3, 11.8 and 12.9, 11.9 and 12.1
+//     (f = 4096, one round: 10.8 and 10.6 at d = 2048 in groups of 32; more
+//     weights: d = 2560, f = 12288 18.2 and 16.5; three tokens: 13.7 and 10.7 at
+//     d = 2048, f = 5120 in groups of 128);
+//   2-bit linears of one step (k <= 512): one matrix of 1024 rows 3.6 and 4.0, of
+//     65536 8.4 and 8.6, of 151936 15.6 and 12.6; 20 of 1024 rows 5.1 and 6.7, 8
+//     4.9 and 4.3, 36 of 2048 11.5 and 8.8.
+bool two_token_gateup(const qmlp_mlp* mlp, int nb) {
+    const qmlp_qweight& w = mlp->gate;
+    const long weights = (long)w.n_out * w.k_in;
+    return nb == 1 && w.bits == 2 && w.n_out / 16 > device_cus() && w.k_in < 4096 &&
+           (w.group == 32   ? weights < (w.n_out <= 8192 ? 30000000 : 24000000)
+            : w.group == 64 ? weights < 24000000
+                            : w.k_in < 2048 && w.n_out > 6144);
+}
+bool two_token_linear(const qmlp_qweight* w, int nb) {
+    const long tiles = (long)nb * w->n_out / 16, cus = device_cus();
+    return w->bits == 2 && w->k_in <= 512 &&
+           (nb == 1 ? tiles <= 16 * cus : tiles >= 3 * cus && tiles <= 9 * cus);
+}
+
+// The slices of k that a batch of nb such linears takes on the tile kernels
+// (0: stand-alone), and whether the gate/up half of nb such blocks runs there.
+int tile_slices(const qmlp_qweight* w, int M, int nb) {
+    if (M == 1 && ((long)nb * w->n_out * w->k_in < kTileOneToken || w->k_in < 6144))
+        return 0;
+    if (M == 2 && two_token_linear(w, nb))
+        return 0;
+    return tile_linear_slices(M, w->n_out, w->k_in, w->group, w->bits, nb);
+}
 bool tile_gateup(const qmlp_mlp* mlp, int M, int nb) {
     const qmlp_qweight& w = mlp->gate;
     if (M == 1 && ((long)nb * w.n_out * w.k_in < kTileOneToken || w.group < 64 || w.k_in < 2048))
         return false;
+    if (M == 2 && two_token_gateup(mlp, nb) && tile_slices(&mlp->down, M, nb) <= 1)
+        return false;                                    // (more slices of down need it there)
     return tile_gateup_supported(M, w.k_in, w.n_out, w.group, w.bits, mlp->rank, nb);
-}
-int tile_slices(const qmlp_qweight* w, int M, int nb) {
-    if (M == 1 && ((long)nb * w->n_out * w->k_in < kTileOneToken || w->k_in < 6144))
-        return 0;
-    return tile_linear_slices(M, w->n_out, w->k_in, w->group, w->bits, nb);
 }
 
 // Workspace: [control words, 1 KB][t: fp32][h: M x f activation type]
@@ -326,11 +356,12 @@ BatchArgs block_batch(const qmlp_mlp* mlp, int M) {
 // 8.0 us of a Qwen3-8B-shaped block at M = 8 where four take 4.5.
 qmlp_status run_gateup(const qmlp_mlp* mlp, const void* x, int M, uint16_t* h, const Workspace& w, int sk,
                        hipStream_t st) {
-    if (block_tile_gateup(mlp, M)) {
+    const bool alone = h != w.h;
+    if (block_tile_gateup(mlp, M) && !(alone && M == 2 && two_token_gateup(mlp, 1))) {
         BatchArgs b = block_batch(mlp, M);
         b.x = static_cast<const uint16_t*>(x);
         b.h = h;
-        const bool own_h = h != w.h && tile_t_bytes(mlp, M) <= ws_h_bytes(mlp, M);
+        const bool own_h = alone && tile_t_bytes(mlp, M) <= ws_h_bytes(mlp, M);
         b.t = sk > 0 ? w.tile_t : own_h ? reinterpret_cast<float*>(w.h) : w.t;
         const int ts = sk > 0 || own_h ? kLoraSlices : 1;
         hipError_t e = mlp->rank > 0 ? launch_lora_a_tile(b, 1, ts, st) : hipSuccess;
