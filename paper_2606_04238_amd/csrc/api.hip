@@ -99,11 +99,12 @@ bool fused_mlp(const qmlp_mlp* mlp, int M) {
 }
 
 // Which halves run on the matrix-core tile kernels (decode_tile.hip) instead
-// of the stand-alone ones: from two tokens on every one that fits.  At one
-// token the stand-alone kernels' arithmetic still fits beside the weight
-// stream and they start sooner, so only large batches gain (kTileOneToken
-// weights per matrix; four blocks of d = 2560, f = 9728 lost, 45 against 49 us),
-// and of those (us, stand-alone and tile):
+// of the stand-alone ones: from two tokens on every one that fits, but for the
+// short rows at two tokens below.  At one token the stand-alone kernels'
+// arithmetic still fits beside the weight stream and they start sooner, so
+// only large batches gain (kTileOneToken weights per matrix; four blocks of
+// d = 2560, f = 9728 lost, 45 against 49 us), and of those (us, stand-alone and
+// tile):
 //   gate/up in groups of 64 or more of long rows: 36 blocks of d = 2560, 4 bits
 //     299 and 271, 2 bits 214 and 202, 12 of d = 4608 116 and 107 (20 of d =
 //     2880 65 and 65; 4 bits in groups of 32 300 and 331, 2 bits 259 and 312);
