@@ -64,7 +64,8 @@ from paper_2606_04238_amd.profiling import read_traffic  # noqa: E402
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 # the kernels of one step of qmlp_forward_layers on each path, as named in
 # the kernel trace (profile summaries); the streamed gate/up launch also
-# computes LoRA-A
+# computes LoRA-A, and every several-token configuration here runs the tile
+# kernels (only gate/up rows past 6144 codes run others on that path)
 STEP_KERNELS = {"streamed": "gu_stream_kernel|dn_stream_kernel",
                 "mfma": "tile_lora_kernel|tile_kernel<2|tile_kernel<4"}
 METRIC = BASE_METRIC = ("achieved HBM GB/s (% of MI355X peak) and µs per W4/W2-GateUp MLP "
